@@ -30,7 +30,7 @@
 // Weights reach the kernels through per-chunk images that a small packing
 // kernel writes into the workspace in LDS order (bank-permuted rows, the
 // contraction slots of the accumulator-fed operands already in accumulator
-// order); a workgroup streams them into a two-slot LDS ring.
+// order); a workgroup streams them into an LDS ring.
 #include <algorithm>
 
 #include "dma.h"
@@ -48,9 +48,9 @@ constexpr int TRN_THREADS = 64 * TRN_WAVES;
 constexpr int TRN_NT = TRN_C / 16;  // MFMA steps over the features
 constexpr int TRN_ROWS = 32 * TRN_WAVES;  // rows per workgroup block
 
-// image layout of one chunk j (hidden columns fb = 32 j .. fb + 31):
-//   forward : A1a [0, 8K)  A1b [8K, 16K)  A2 [16K, 24K)
-//   backward: A1a [0, 8K)  A1b [8K, 16K)  A3 [16K, 24K)  A4 [24K, 40K)
+// image layout of one chunk j (hidden columns fb = 32 j .. fb + 31), bytes:
+//   forward : A1a [0, 8K)    A1b [8K, 16K)    A2 [16K, 24K)
+//   backward: A1a [0, 8.5K)  A1b [8.5K, 17K)  A3 [17K, 25.5K)  A4 [25.5K, 43.5K), padded to 44K
 // A1a / A1b: W1^T rows fb + r (a) / F + fb + r (b), 16 chunks of 8 features.
 // A2: W2^T for output tile t, row r = output column 32 t + r, 4 chunks
 //     (k-step s, half g) of hidden columns in accumulator order.
@@ -58,17 +58,22 @@ constexpr int TRN_ROWS = 32 * TRN_WAVES;  // rows per workgroup block
 // A4: W1 for feature tile t, row r = feature 32 t + r, 8 chunks (k-step
 //     s = 0..3, half g): s < 2 the a columns, s >= 2 the b columns of the
 //     chunk, in accumulator order.
-constexpr int OFF_A1B = 8192, OFF_A2 = 16384, OFF_A3 = 16384, OFF_A4 = 24576;
+// Forward rows are bank-permuted (below).  Every backward row is followed by
+// 16 unused bytes instead: rows r, r + 1, .. then start an odd number of
+// 16-byte pieces apart, so an operand read (one piece of 32 consecutive
+// rows) is free of bank conflicts and all of a lane's reads of a chunk are
+// one address plus constants (the permutation takes 24 address registers,
+// which the dx kernel spends on operands in flight instead).
+constexpr int OFF_A1B = 8192, OFF_A2 = 16384;                     // forward
+constexpr int P1 = 256 + 16, P4 = 128 + 16;                       // backward row pitches
+constexpr int OFF_B1B = 32 * P1, OFF_A3 = 64 * P1, OFF_A4 = 96 * P1;
+static_assert(OFF_A4 + 128 * P4 <= TRN_BWD_IMG && TRN_BWD_IMG % 1024 == 0, "image size");
 
 // 256-byte rows: chunk c of row r at slot c ^ (r % 16).
 __device__ inline uint32_t w256_off(int r, int c) { return r * 256 + 16 * (c ^ (r & 15)); }
 // A2 tile rows of 64 bytes.
 __device__ inline uint32_t a2_off(int t, int r, int c) {
   return t * 2048 + r * 64 + 16 * (c ^ ((r >> 2) & 3));
-}
-// A4 tile rows of 128 bytes.
-__device__ inline uint32_t a4_off(int t, int r, int c) {
-  return t * 4096 + r * 128 + 16 * (c ^ ((r >> 1) & 7));
 }
 // Accumulator order of a 16-wide contraction step s: slot e of half g holds
 // index 16 s + 8 (e / 4) + 4 g + e % 4 (the rows a 32x32 accumulator gives
@@ -83,37 +88,42 @@ __device__ inline f32x4 mma16(bf16x8 a, bf16x8 b, f32x4 c) {
 
 // ---- weight images -------------------------------------------------------------------
 
-// One thread per 16-byte slot of the images of all chunks.
+// One thread per 16-byte piece of the images of all chunks.
 __global__ __launch_bounds__(256) void trn_pack_kernel(const bf16* w1, const bf16* w2, int f,
                                                        int bwd, char* img) {
   const int img_bytes = bwd ? TRN_BWD_IMG : TRN_FWD_IMG;
   const int per = img_bytes / 16;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= (int64_t)(f / TRN_FC) * per) return;
-  const int j = (int)(idx / per), q = (int)(idx % per), fb = TRN_FC * j;
+  const int j = (int)(idx / per), q = (int)(idx % per), o = 16 * q, fb = TRN_FC * j;
   const int n1 = 2 * f;  // W1 row length
-  bf16x8 v;
-  if (q < 1024) {  // A1a, A1b
-    const int r = (q & 511) >> 4, c = (q & 15) ^ (r & 15);
-    const int col = (q < 512 ? 0 : f) + fb + r;
+  bf16x8 v = {};         // padding pieces stay zero
+  if (bwd ? o < OFF_A3 : q < 1024) {  // A1a, A1b
+    const int half = bwd ? o / OFF_B1B : q >> 9;
+    const int r = bwd ? o % OFF_B1B / P1 : (q & 511) >> 4;
+    const int c = bwd ? (o % OFF_B1B % P1) >> 4 : (q & 15) ^ (r & 15);
+    const int col = half * f + fb + r;
+    if (c < 16) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = w1[(int64_t)(8 * c + e) * n1 + col];
+      for (int e = 0; e < 8; ++e) v[e] = w1[(int64_t)(8 * c + e) * n1 + col];
+    }
   } else if (!bwd) {  // A2
     const int q2 = q - 1024, t = q2 >> 7, r = (q2 & 127) >> 2, c = (q2 & 3) ^ ((r >> 2) & 3);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = w2[(int64_t)(fb + acc_k(c >> 1, c & 1, e)) * TRN_C + 32 * t + r];
-  } else if (q < 1536) {  // A3
-    const int q3 = q - 1024, r = q3 >> 4, c = (q3 & 15) ^ (r & 15);
-    v = *(const bf16x8*)(w2 + (int64_t)(fb + r) * TRN_C + 8 * c);
+  } else if (o < OFF_A4) {  // A3
+    const int r = (o - OFF_A3) / P1, c = ((o - OFF_A3) % P1) >> 4;
+    if (c < 16) v = *(const bf16x8*)(w2 + (int64_t)(fb + r) * TRN_C + 8 * c);
   } else {  // A4
-    const int q4 = q - 1536, t = q4 >> 8, r = (q4 & 255) >> 3, c = (q4 & 7) ^ ((r >> 1) & 7);
+    const int r = (o - OFF_A4) / P4, c = ((o - OFF_A4) % P4) >> 4;  // r: feature
     const int s = c >> 1, g = c & 1;
     const int base = (s < 2 ? 0 : f) + fb;
+    if (r < TRN_C && c < 8) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = w1[(int64_t)(32 * t + r) * n1 + base + acc_k(s & 1, g, e)];
+      for (int e = 0; e < 8; ++e) v[e] = w1[(int64_t)r * n1 + base + acc_k(s & 1, g, e)];
+    }
   }
-  // write the slot where the reader expects it (the index already is the slot)
-  *(bf16x8*)(img + (int64_t)j * img_bytes + 16 * q) = v;
+  *(bf16x8*)(img + (int64_t)j * img_bytes + o) = v;
 }
 
 // Stream chunk images through a two-slot LDS ring: each thread copies
@@ -283,34 +293,83 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_fwd_kernel(TrnFwdArgs a) {
 
 // ---- backward: dx ----------------------------------------------------------------------
 
+// One chunk image HBM -> LDS by DMA, 1 KB pieces dealt to the waves in turn
+// (the last piece several times, so that no wave branches; real = false reads
+// no memory and fills the slot with zeros).
+template <int IMG>
+__device__ inline void chunk_dma(const char* src, char* dst, int wave, int lane, bool real) {
+  constexpr int PIECES = IMG / 1024;
+  static_assert(IMG % 1024 == 0, "whole pieces");
+  const rsrc_t r = buf_rsrc_n(src, real ? (uint32_t)IMG : 0u);
+#pragma unroll
+  for (int i = 0; i < (PIECES + TRN_WAVES - 1) / TRN_WAVES; ++i) {
+    const int piece = min(wave + TRN_WAVES * i, PIECES - 1);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (TRIATTN_LDS void*)(dst + 1024 * piece), 16,
+                                             16 * lane, 1024 * piece, 0, 0);
+  }
+}
+
+// Persistent workgroups of 8 waves as in the forward, 32 rows per wave.  Per
+// chunk a wave forms du, ha and hb (24 MFMAs) and adds the chunk's share of
+// do1 (16).  The chunk images arrive in a ring of three by DMA; a wave's
+// operand reads run TRN_NQ fragments ahead of their use, across chunks, and
+// the elementwise step is dealt over the MFMAs after ha in stages of a pair
+// of elements, so that it waits for neither.  Weights copied through
+// registers and reads left to the compiler (one fragment ahead) measured
+// 483 us at m = 768^2, F = 512, against 456 us on the same card (845 TFLOP/s
+// of the ten products).  Of what remains the operand reads, one LDS fragment
+// per MFMA, cost most (without them, a third less); 64 rows per wave would
+// halve them, but at one wave per SIMD the forward built that way was slower
+// (314 against 268 us).
+
+constexpr int TRN_NQ = 8;  // operand fragments in flight per wave
+
 __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_dx_kernel(TrnBwdArgs a) {
-  __shared__ __align__(16) char ring[2][TRN_BWD_IMG];
+  constexpr int SLOTS = 3, NQ = TRN_NQ;
+  __shared__ __align__(16) char ring[SLOTS * TRN_BWD_IMG];
   __shared__ __align__(16) float gb[2][TRN_C];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t nblk = (a.m + TRN_ROWS - 1) / TRN_ROWS;
   if ((int64_t)blockIdx.x >= nblk) return;
   const int nch = a.f / TRN_FC;
   const int64_t nsteps = (nblk - blockIdx.x + gridDim.x - 1) / gridDim.x * nch;
-  constexpr int PER = TRN_BWD_IMG / 16 / TRN_THREADS;
-  Stage<PER> st;
-  st.load(a.img, tid);
+  int dj = 0, ds = 0;  // chunk index and slot of the next DMA
+  int64_t issued = 0;
+  auto issue = [&] {
+    chunk_dma<TRN_BWD_IMG>(a.img + (int64_t)dj * TRN_BWD_IMG, ring + ds * TRN_BWD_IMG, wave, lane,
+                           issued < nsteps);
+    dj = dj + 1 == nch ? 0 : dj + 1;
+    ds = ds + 1 == SLOTS ? 0 : ds + 1;
+    ++issued;
+  };
+  issue();
+  issue();
   if (tid < TRN_C) {
     gb[0][tid] = (float)a.gamma[tid];
     gb[1][tid] = (float)a.beta[tid];
   }
-  st.store(ring[0], tid);
+  wait_vm<0>();
   __syncthreads();
 
-  uint32_t a1[TRN_NT], a4[4][4];
+  const uint32_t base = lds_addr(ring);
+  const uint32_t b1 = base + l32 * P1 + 16 * g, b4 = base + OFF_A4 + l32 * P4 + 16 * g;
+  uint32_t so = 0;  // slot offset of the current chunk
+  // operand fragments of a chunk in the order of use: A3 (du), A1a (ha), A1b
+  // (hb), 8 steps each, then A4 of the b columns (steps 2, 3) and of the a
+  // columns (steps 0, 1), four feature tiles each
+  bf16x8 fq[NQ];
+  auto frag = [&](uint32_t o, int i) {
+    if (i < 24) {
+      const int off = i < 8 ? OFF_A3 : (i < 16 ? 0 : OFF_B1B);
+      return lds_load16<bf16x8>(b1 + o + off + 32 * (i & 7));
+    }
+    const int s = ((i - 24) >> 2) ^ 2, t = i & 3;
+    return lds_load16<bf16x8>(b4 + o + t * 32 * P4 + 32 * s);
+  };
 #pragma unroll
-  for (int t = 0; t < TRN_NT; ++t) a1[t] = w256_off(l32, 2 * t + g);
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int s = 0; s < 4; ++s) a4[t][s] = OFF_A4 + a4_off(t, l32, 2 * s + g);
+  for (int i = 0; i < NQ; ++i) fq[i] = frag(0, i);
 
-  int64_t step = 0;
   for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
     const int64_t row = blk * TRN_ROWS + wave * 32 + l32;
     const int64_t rc = row < a.m ? row : a.m - 1;
@@ -320,27 +379,60 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_dx_kernel(TrnBwdArgs a
     const float mean = a.mean[rc], rstd = a.rstd[rc];
     ln_row_saved(xr, gb, g, mean, rstd, of);
     f32x16 d1[4] = {};  // do1^T: feature 32 t + acc row, lane <-> row
-    for (int j = 0; j < nch; ++j, ++step) {
-      const char* cur = ring[step & 1];
-      const bool more = step + 1 < nsteps;
-      if (more) st.load(a.img + (int64_t)(j + 1 == nch ? 0 : j + 1) * TRN_BWD_IMG, tid);
-      const f32x16 ha = h_tile(cur, a1, of);
-      const f32x16 hb = h_tile(cur + OFF_A1B, a1, of);
-      const f32x16 du = h_tile(cur + OFF_A3, a1, df);  // du^T = W2 rows . dout^T
+    for (int j = 0; j < nch; ++j) {
+      const uint32_t sn = so == (SLOTS - 1) * TRN_BWD_IMG ? 0u : so + TRN_BWD_IMG;
+      f32x16 ha = {}, hb = {}, du = {};
       bf16x8 dh[4];
+      float ex[16], si[16], sg[16];
+      // elementwise work that goes with MFMA w, a pair of elements per stage:
+      // dh[0], dh[1] = da and dh[2], dh[3] = db
+      auto valu = [&](int w) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float x = ha[v], sg = sigm(x), silu = x * sg;
-        dh[v >> 3][v & 7] = (bf16)(du[v] * hb[v] * sg * (1.f + x * (1.f - sg)));
-        dh[2 + (v >> 3)][v & 7] = (bf16)(du[v] * silu);
+        for (int k = 0; k < 2; ++k) {
+          const int e0 = 2 * (w - 17) + k, e1 = e0 - 2, e2 = e0 - 4, eb = e0 - 6, ea = 2 * (w - 26) + k;
+          if (e0 >= 0 && e0 < 16) ex[e0] = __builtin_amdgcn_exp2f(-LOG2E * ha[e0]);
+          if (e1 >= 0 && e1 < 16) ex[e1] = __builtin_amdgcn_rcpf(1.f + ex[e1]);
+          if (e2 >= 0 && e2 < 16) {
+            si[e2] = ha[e2] * ex[e2];                     // a sigmoid(a)
+            sg[e2] = fmaf(si[e2], 1.f - ex[e2], ex[e2]);  // sigmoid(a) (1 + a (1 - sigmoid(a)))
+          }
+          if (eb >= 0 && eb < 16) dh[2 + (eb >> 3)][eb & 7] = (bf16)(du[eb] * si[eb]);
+          if (ea >= 0 && ea < 16) dh[ea >> 3][ea & 7] = (bf16)(du[ea] * hb[ea] * sg[ea]);
+        }
+      };
+      auto refill = [&](int i) {
+        fq[i % NQ] = i + NQ < 40 ? frag(so, i + NQ) : frag(sn, i + NQ - 40);
+      };
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        du = Mma<bf16>::mma(fq[i % NQ], df[i], du);  // du^T = W2 rows . dout^T
+        refill(i);
+        __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
+      for (int i = 8; i < 16; ++i) {
+        ha = Mma<bf16>::mma(fq[i % NQ], of[i - 8], ha);
+        refill(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-          d1[t] = Mma<bf16>::mma(*(const bf16x8*)(cur + a4[t][s]), dh[s], d1[t]);
-      if (more) st.store(ring[(step + 1) & 1], tid);
-      __syncthreads();
+      for (int i = 16; i < 24; ++i) {
+        hb = Mma<bf16>::mma(fq[i % NQ], of[i - 16], hb);
+        refill(i);
+        valu(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      wait_vm<0>();  // the next chunk has landed; every wave has left the previous one
+      lds_barrier();
+      issue();
+#pragma unroll
+      for (int i = 24; i < 40; ++i) {
+        d1[i & 3] = Mma<bf16>::mma(fq[i % NQ], dh[((i - 24) >> 2) ^ 2], d1[i & 3]);
+        refill(i);
+        valu(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      so = sn;
     }
     // layer-norm backward: wdy = do1 gamma, dx = rstd (wdy - c1 xhat - c2)
     float xh[4][16], wdy[4][16];
@@ -369,6 +461,7 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_dx_kernel(TrnBwdArgs a
       for (int v = 0; v < 16; ++v) dx[t][v] = (wdy[t][v] - c1 * xh[t][v] - c2) * rstd;
     if (row < a.m) store_row(a.dx, row, g, dx);
   }
+  wait_vm<0>();  // the copies past the last chunk land before the workgroup ends
 }
 
 // ---- backward: sums over rows ----------------------------------------------------------
@@ -444,9 +537,9 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_w_kernel(TrnBwdArgs a,
   bf16x8 w1a[4], w1b[4], w2r[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    const char* o = img + w256_off((f0 & 31) + l16, 4 * s + q);
+    const char* o = img + ((f0 & 31) + l16) * P1 + 16 * (4 * s + q);
     w1a[s] = *(const bf16x8*)o;
-    w1b[s] = *(const bf16x8*)(o + OFF_A1B);
+    w1b[s] = *(const bf16x8*)(o + OFF_B1B);
     w2r[s] = *(const bf16x8*)(o + OFF_A3);
   }
 
@@ -593,12 +686,14 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_w_kernel(TrnBwdArgs a,
   }
 }
 
-// Fixed-order sum of the partial blocks: G and s into gsum, dW2 into its output.
+// Fixed-order sum of the partial blocks: G and s into gsum (part 0's place:
+// an entry is read and written by one thread only), dW2 into its output.
 __global__ __launch_bounds__(256) void trn_reduce_kernel(TrnBwdArgs a) {
   const int64_t per = trn_part_floats(a.f);
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= per) return;
   float s = 0.f;
+#pragma unroll 16
   for (int p = 0; p < a.nparts; ++p) s += a.part[(int64_t)p * per + i];
   const int64_t ng = (int64_t)TRN_C * 2 * a.f + 2 * a.f;
   if (i < ng)
