@@ -160,9 +160,7 @@ int run_bwd(int node, const Geom& g, const Layout& L, const void* q, const void*
   const triattn::BwdWs w{(float*)(b + L.lse2), (float*)(b + L.dsum), (void*)(b + L.da),
                          std::is_same<T, float>::value ? nullptr : (void*)(b + L.dalo),
                          (float*)(b + L.slabs), L.nrc};
-  if (triattn::launch_prep<T>(g, node, (const T*)bias, mask, p, s) != hipSuccess)
-    return TRIATTN_ERR_HIP;
-  if (triattn::launch_bwd<T>(g, node, p, w, (const T*)q, (const T*)k, (const T*)v,
+  if (triattn::launch_bwd<T>(g, node, p, w, (const T*)bias, mask, (const T*)q, (const T*)k, (const T*)v,
                              (const T*)gate, (const T*)out, lse, (const T*)dout, (T*)dq, (T*)dk,
                              (T*)dv, (T*)dg, (T*)dbias, dbias_f32, s) != hipSuccess)
     return TRIATTN_ERR_HIP;

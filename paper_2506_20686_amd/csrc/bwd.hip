@@ -8,7 +8,8 @@
 //              dA is kept as a pair hi + lo of bf16 numbers and dP = dA V^T
 //              takes both (one extra MFMA): rounding dA to a single bf16
 //              makes sum_k P dP drift from D, and that drift accumulates
-//              in the row sum of the bias gradient.
+//              in the row sum of the bias gradient.  The same launch prepares
+//              the bias and the key bits (prep.h).
 //   dkdv     : the paper's first stage -- per (row, head, key block), loop
 //              over query tiles: dV += P^T dA, dK += scale dS^T Q (in
 //              dkdv.hip, launched from here).
@@ -30,6 +31,7 @@
 #include "bwd.h"
 #include "dma.h"
 #include "kernels.h"
+#include "prep.h"
 #include "stage.h"
 #include "timing.h"
 
@@ -41,9 +43,9 @@ namespace triattn {
 // 8 TPH c + 8 (t % TPH) .. +7 for c < NC, so every load and store is 16
 // contiguous bytes (bf16) and a wave covers 16 (32) whole (pair, head) rows.  All of a thread's loads are
 // issued before its first store (the compiler may not move loads past stores
-// to memory that could alias them).  Grid: x over the (b, h) entries of one
-// pair row a = blockIdx.y (all index arithmetic in 32 bits but the row
-// offset).
+// to memory that could alias them).  A workgroup takes the (b, h) entries
+// 256 xblk / TPH .. of one pair row pa (all index arithmetic in 32 bits but
+// the row offset).
 template <typename T>
 struct Vec8 {
   float x[8];
@@ -76,11 +78,10 @@ __device__ inline void store8(float* p, const float (&x)[8]) {
   *(f32x4*)(p + 4) = f32x4{x[4], x[5], x[6], x[7]};
 }
 
-template <typename T, int D = HEAD_DIM>
-__global__ __launch_bounds__(256) void bwd_prep_kernel(Geom G, int node, const T* out,
-                                                       const float* lse, const T* gate,
-                                                       const T* dout, T* dg, T* da,
-                                                       T* dalo, float* lse2) {
+template <typename T, int D>
+__device__ inline void bwd_elementwise(const Geom& G, int node, int pa, int xblk, const T* out,
+                                       const float* lse, const T* gate, const T* dout, T* dg,
+                                       T* da, T* dalo, float* lse2) {
   out = at_sample(out, G.bPair);
   gate = at_sample(gate, G.bPair);
   dout = at_sample(dout, G.bPair);
@@ -92,10 +93,9 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(Geom G, int node, const T
   constexpr int TPH = D == 16 ? 2 : 4;  // threads per (pair, head)
   constexpr int NC = D / (8 * TPH);     // 8-channel chunks per thread
   constexpr int CS = 8 * TPH;           // channel stride between a thread's chunks
-  const uint32_t tix = blockIdx.x * 256u + threadIdx.x;
+  const uint32_t tix = (uint32_t)xblk * 256u + threadIdx.x;
   const uint32_t in_row = tix / TPH;  // b * H + h
   if (in_row >= (uint32_t)(G.n * G.H)) return;
-  const int pa = blockIdx.y;
   const int64_t idx = (int64_t)pa * (G.n * G.H) + in_row;  // (a, b, h)
   const int64_t base = idx * D + 8 * (tix % TPH);
   Vec8<T> go[NC], oo[NC], gg[NC];
@@ -128,16 +128,49 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(Geom G, int node, const T
 }
 
 // Queries n .. np-1 of every row: no valid key (+inf) and D = 0.
-__global__ __launch_bounds__(256) void bwd_pad_kernel(Geom G, float* lse2, float* dsum) {
+__device__ inline void bwd_pad(const Geom& G, int block, float* lse2, float* dsum) {
   lse2 = ws_at_sample(lse2, G.bWs);
   dsum = ws_at_sample(dsum, G.bWs);
   const int pad = G.np - G.n;
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t idx = (int64_t)block * 256 + threadIdx.x;
   if (idx >= (int64_t)G.H * G.nr * pad) return;
   const int64_t hr = idx / pad;
   const int64_t at = hr * G.np + G.n + (int)(idx % pad);
   lse2[at] = pos_inf();
   dsum[at] = 0.f;
+}
+
+// Everything the backward's kernels read besides the caller's tensors, in one
+// launch: the pieces of prep.h (blocks [0, nprep)), the padding queries
+// ([nprep, nprep + npad)) and the elementwise step (the rest, ew blocks per
+// pair row).  Measured in one launch at N = 384 / 768 (32 channels) and 333
+// (64 channels): 39.5 / 160 / 58.5 us, what the elementwise step took by
+// itself; the other pieces (11, 14 and 17 us as launches of their own) run
+// under it.  Four waves per SIMD feed the HBM as well as eight, and 64
+// registers (eight waves) spill the bias piece: 167 us at N = 768.
+struct BwdPrepGrid {
+  int nkb, nprep, npad, ew;
+};
+template <typename T, int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void bwd_prep_kernel(
+                                                       Geom G, int node, BwdPrepGrid pg,
+                                                       const T* bias, const uint8_t* mask, Prep p,
+                                                       const T* out, const float* lse,
+                                                       const T* gate, const T* dout, T* dg, T* da,
+                                                       T* dalo, float* lse2, float* dsum) {
+  int b = (int)blockIdx.x;
+  if (b < pg.nprep) {
+    prep_block(G, node, b, pg.nkb, bias, mask, p);
+    return;
+  }
+  b -= pg.nprep;
+  if (b < pg.npad) {
+    bwd_pad(G, b, lse2, dsum);
+    return;
+  }
+  b -= pg.npad;
+  const int pa = b / pg.ew;
+  bwd_elementwise<T, D>(G, node, pa, b - pa * pg.ew, out, lse, gate, dout, dg, da, dalo, lse2);
 }
 
 // ---- dQ (and D) ----------------------------------------------------------------------
@@ -1247,9 +1280,9 @@ __global__ __launch_bounds__(256) void db_reduce_kernel(Geom G, int node, int nr
 }
 
 template <typename T>
-hipError_t launch_bwd(const Geom& g, int node, const Prep& p, const BwdWs& ws, const T* q,
-                      const T* k, const T* v, const T* gate, const T* out, const float* lse,
-                      const T* dout, T* dq, T* dk, T* dv, T* dg, T* dbias, float* dbias_f32,
+hipError_t launch_bwd(const Geom& g, int node, const Prep& p, const BwdWs& ws, const T* bias,
+                      const uint8_t* mask, const T* q, const T* k, const T* v, const T* gate,
+                      const T* out, const float* lse, const T* dout, T* dq, T* dk, T* dv, T* dg, T* dbias, float* dbias_f32,
                       hipStream_t s) {
   T* da = (T*)ws.da;
   T* dalo = (T*)ws.dalo;
@@ -1258,23 +1291,27 @@ hipError_t launch_bwd(const Geom& g, int node, const Prep& p, const BwdWs& ws, c
   if (d16 && !std::is_same<T, bf16>::value) return hipErrorInvalidValue;
   {
     KernelTimer t(K_BWD_PREP, s);
-    const dim3 grid((unsigned)((4 * g.n * g.H + 255) / 256), (unsigned)g.nr, (unsigned)g.batch);
-    if (d64)
-      hipLaunchKernelGGL((bwd_prep_kernel<T, 64>), grid, dim3(256), 0, s, g, node, out, lse, gate,
-                         dout, dg, da, dalo, ws.lse2);
-    else if (d16)  // two threads per (pair, head): half the grid
-      hipLaunchKernelGGL((bwd_prep_kernel<T, 16>),
-                         dim3((unsigned)((2 * g.n * g.H + 255) / 256), (unsigned)g.nr, (unsigned)g.batch),
-                         dim3(256), 0, s, g, node, out, lse, gate, dout, dg, da, dalo, ws.lse2);
-    else
-      hipLaunchKernelGGL((bwd_prep_kernel<T, 32>), grid, dim3(256), 0, s, g, node, out, lse, gate,
-                         dout, dg, da, dalo, ws.lse2);
-  }
-  if (g.np > g.n) {
-    const int64_t npad = (int64_t)g.H * g.nr * (g.np - g.n);
-    KernelTimer t(K_BWD_PAD, s);
-    hipLaunchKernelGGL(bwd_pad_kernel, dim3((unsigned)((npad + 255) / 256), 1, (unsigned)g.batch), dim3(256), 0, s, g,
-                       ws.lse2, ws.dsum);
+    const int tph = d16 ? 2 : 4;  // threads per (pair, head) of the elementwise step
+    BwdPrepGrid pg;
+    pg.nkb = (int)prep_kbits_blocks(g, node);
+    pg.nprep = (int)prep_blocks(g, node);
+    pg.npad = (int)(((int64_t)g.H * g.nr * (g.np - g.n) + 255) / 256);
+    pg.ew = (tph * g.n * g.H + 255) / 256;
+    // (a pair map whose grid passes 2^32 threads, n nr H >= 2^30, has tensors
+    // of 34 GB and up, a dozen of which no card holds)
+    const dim3 grid((unsigned)(pg.nprep + pg.npad) + (unsigned)pg.ew * (unsigned)g.nr, 1,
+                    (unsigned)g.batch);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, g, node, pg, bias, mask, p, out, lse, gate,
+                         dout, dg, da, dalo, ws.lse2, ws.dsum);
+    };
+    if (d64) {
+      go(bwd_prep_kernel<T, 64>);
+    } else if (d16) {
+      if constexpr (std::is_same<T, bf16>::value) go(bwd_prep_kernel<T, 16>);
+    } else {
+      go(bwd_prep_kernel<T, 32>);
+    }
   }
   BwdArgs<T> a{g, p.bt, p.btT, p.kbits, p.rowfull, q, k, v, da, dalo, ws.lse2, ws.dsum, dq, dk, dv, ws.slabs,
                (g.n + BWD_BLK - 1) / BWD_BLK, ws.nrc, (g.nr + ws.nrc - 1) / ws.nrc};
@@ -1338,10 +1375,12 @@ hipError_t launch_bwd(const Geom& g, int node, const Prep& p, const BwdWs& ws, c
 }
 
 template hipError_t launch_bwd<bf16>(const Geom&, int, const Prep&, const BwdWs&, const bf16*,
+                                     const uint8_t*, const bf16*,
                                      const bf16*, const bf16*, const bf16*, const bf16*,
                                      const float*, const bf16*, bf16*, bf16*, bf16*, bf16*,
                                      bf16*, float*, hipStream_t);
 template hipError_t launch_bwd<float>(const Geom&, int, const Prep&, const BwdWs&, const float*,
+                                      const uint8_t*, const float*,
                                       const float*, const float*, const float*, const float*,
                                       const float*, const float*, float*, float*, float*, float*,
                                       float*, float*, hipStream_t);

@@ -72,12 +72,13 @@ hipError_t launch_prep(const Geom& g, int node, const T* bias, const uint8_t* ma
 template <typename T>
 hipError_t launch_fwd(const Geom& g, const Prep& p, const T* q, const T* k, const T* v,
                       const T* gate, T* out, float* lse, hipStream_t s);
+// launch_bwd also makes its own preparation (launch_prep is the forward's).
 // dbias_f32, when not null, receives the bias gradient in fp32 (a row range's
 // partial sum, to be added to other ranges' before rounding) and dbias is unused.
 template <typename T>
-hipError_t launch_bwd(const Geom& g, int node, const Prep& p, const BwdWs& w, const T* q,
-                      const T* k, const T* v, const T* gate, const T* out, const float* lse,
-                      const T* dout, T* dq, T* dk, T* dv, T* dg, T* dbias, float* dbias_f32,
+hipError_t launch_bwd(const Geom& g, int node, const Prep& p, const BwdWs& w, const T* bias,
+                      const uint8_t* mask, const T* q, const T* k, const T* v, const T* gate,
+                      const T* out, const float* lse, const T* dout, T* dq, T* dk, T* dv, T* dg, T* dbias, float* dbias_f32,
                       hipStream_t s);
 
 // d = 16 through the d = 32 kernels (pad.hip): rows of 16 channels copied

@@ -7,11 +7,9 @@
 namespace triattn {
 
 enum KernelId {
-  K_PREP_BIAS,
-  K_PREP_KBITS,
+  K_PREP,
   K_FWD,
   K_BWD_PREP,
-  K_BWD_PAD,
   K_DQ,
   K_DKDV,
   K_DB,
