@@ -42,21 +42,30 @@ bool padded16(int64_t d, int dtype) { return d == 16 && dtype != TRIATTN_BF16; }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-// Row chunks of the bias-gradient reduction over nr rows (at most 16 partial
-// slabs).  Each workgroup of the bias-gradient kernel takes 128 queries x 128
-// keys of one head over one chunk of rows and fills a CU on its own, so the
-// kernel runs in rounds of 256 workgroups.  The cost model, in units of one
-// row's work: per round the chunk's rows plus about 3.3 for the workgroup's
-// fixed work (bias tile, pipeline fill, slab store), plus about 1 per slab
-// for the reduction that reads the slabs back.
+// Row chunks of the bias-gradient reduction over nr rows (partial slabs).
+// Each workgroup of the bias-gradient kernel takes 128 queries x 128 keys of
+// one head over one chunk of rows and fills a CU on its own, so the kernel
+// runs in rounds of 256 workgroups.  The cost model, in units of one row's
+// work: per round the chunk's rows plus about 3.3 for the workgroup's fixed
+// work (bias tile, pipeline fill, slab store), plus, per slab, the reduction
+// that reads it back.  A slab costs about 1 where it is large (N = 768, four
+// heads: 9.4 MB); where sixteen chunks would leave half of the chip idle
+// (tiles <= 8, up to 128 tokens at four heads) its 16 .. 260 KB cost little
+// more than a tenth, and up to 32 chunks are taken.  Measured (events around
+// the launch, 5 us included), before -> after: fp32 N = 32, 4 -> 16 chunks, dB
+// 22.1 -> 10.0 us, its reduction 8.1 -> 8.9; bf16 N = 100, 10 -> 25 chunks,
+// 20.6 -> 15.0 and 16 -> 11.3.
 int db_row_chunks(int64_t n, int64_t nr, int64_t h) {
   const int64_t tiles = h * ((n + 127) / 128) * ((n + 127) / 128);
+  const bool small = tiles <= 8;
+  const double np = (double)((n + 31) / 32 * 32);
+  const double slab = small ? 0.1 + (double)h * np * np / (4.0 * 768 * 768) : 1.0;
   int best = 1;
   double best_cost = 1e300;
-  for (int64_t c = 1; c <= 16 && c <= nr; ++c) {
+  for (int64_t c = 1; c <= (small ? 32 : 16) && c <= nr; ++c) {
     const int64_t rpc = (nr + c - 1) / c, chunks = (nr + rpc - 1) / rpc;
     const int64_t rounds = (tiles * chunks + 255) / 256;
-    const double cost = (double)rounds * ((double)rpc + 3.3) + (double)chunks;
+    const double cost = (double)rounds * ((double)rpc + 3.3) + slab * (double)chunks;
     if (cost < best_cost) {
       best_cost = cost;
       best = (int)chunks;
