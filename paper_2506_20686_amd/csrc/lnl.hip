@@ -869,6 +869,408 @@ __global__ __launch_bounds__(64 * LBG_WAVES) void lnl_bwd_g_kernel(LnlBwdArgs a)
   }
 }
 
+// lnl_bwd: dx and the row sums in one pass over x and dO2, for the shapes of
+// the attention's projection: NW leading outputs of 128 columns (2 to 4) and
+// up to 16 further columns in narrower outputs.  Persistent workgroups of
+// eight waves, one per CU, walk 32-row units; a unit's x, statistics and dO2
+// rows arrive in one of two LDS slots by DMA while the other is worked on.
+// Wave (kt, h) = (w % 4, w / 4) owns features 32 kt .. + 31 and the 32-column
+// tiles T = h + 2 i:
+//   do1^T [32 k][32 rows] += W[k][T] . dO2[rows][T]^T  (partial: its tiles)
+//   G[i]  [32 k][T]       += xhat^T dO2                (kept over all units)
+// Every dO2 tile is read from LDS in both forms, rows and transposed.  The W
+// fragments of its tiles stay with the wave, in registers or (WL tiles) in
+// LDS.  The two partial do1 of a k tile are exchanged half and half through
+// LDS, so that each wave ends with 16 features of 32 rows, 8 consecutive ones
+// per lane; c1 and c2 are summed over the waves through LDS.
+//
+// Slot rows are 256 bytes (one 128-column row of x or of an output), chunk c
+// (8 columns) of row p at chunk slot c ^ (4 (p % 4) + (p / 4) % 4): 16
+// consecutive rows put a chunk on 16 different 16-byte banks (row reads), 4
+// consecutive rows put a run of four chunks on four different 64-byte banks
+// (transposed reads).
+constexpr int LB_WAVES = 8, LB_THREADS = 64 * LB_WAVES;
+constexpr int LB_TAIL = 16;  // columns past the 128-column outputs, at most
+
+template <int NW>
+struct LbL {
+  static constexpr int TPW = 2 * NW;              // 32-column tiles per wave
+  static constexpr int SLOTS = 3;
+  static constexpr int DO = 8192;                 // slot: x, dO2 outputs, mean, rstd, tail, zeros
+  static constexpr int ST = DO + NW * 8192;
+  static constexpr int TL = ST + 256;
+  static constexpr int ZERO = TL + 64 * LB_TAIL;
+  static constexpr int SLOT = ZERO + 64;
+};
+
+__device__ inline int lb_perm(int p) { return 4 * (p & 3) + ((p >> 2) & 3); }
+
+// The operand reads of one tile, one wait: transposed rows at t0 + OFF
+// (positions 0 .. 7 and 16 .. 23) and t1 + OFF (8 .. 15 and 24 .. 31), row
+// fragments at r0 + OFF and r1 + OFF.
+template <int OFF>
+__device__ inline void lb_tile_reads(uint32_t t0, uint32_t t1, uint32_t r0, uint32_t r1, s16x4 (&tr)[4], f32x4 (&rf)[2]) {
+  asm volatile(
+      "ds_read_b128 %4, %8 offset:%10\n\tds_read_b128 %5, %9 offset:%10\n\t"
+      "ds_read_b64_tr_b16 %0, %6 offset:%10\n\tds_read_b64_tr_b16 %1, %7 offset:%11\n\t"
+      "ds_read_b64_tr_b16 %2, %6 offset:%12\n\tds_read_b64_tr_b16 %3, %7 offset:%13\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(tr[0]), "=&v"(tr[1]), "=&v"(tr[2]), "=&v"(tr[3]), "=&v"(rf[0]), "=&v"(rf[1])
+      : "v"(t0), "v"(t1), "v"(r0), "v"(r1), "i"(OFF), "i"(OFF + 2048), "i"(OFF + 4096), "i"(OFF + 6144));
+}
+
+template <int OFF>
+__device__ inline void lb_row_reads(uint32_t r0, uint32_t r1, f32x4 (&rf)[2]) {
+  asm volatile("ds_read_b128 %0, %2 offset:%4\n\tds_read_b128 %1, %3 offset:%4\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(rf[0]), "=&v"(rf[1])
+               : "v"(r0), "v"(r1), "i"(OFF));
+}
+template <int OFF>
+__device__ inline void lb_read16(uint32_t addr, f32x4& v) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(addr), "i"(OFF));
+}
+
+// x^T of the wave's k tile at 16 positions (addresses as above) and their mean
+// and rstd (sp: 4 (lane / 32) positions on), one wait.
+template <int OFF, int ST>
+__device__ inline void lb_x_reads(uint32_t t0, uint32_t t1, uint32_t sp, s16x4& xa, s16x4& xb, f32x4 (&st)[4]) {
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %6 offset:%9\n\tds_read_b64_tr_b16 %1, %7 offset:%10\n\t"
+      "ds_read_b128 %2, %8 offset:%11\n\tds_read_b128 %3, %8 offset:%12\n\t"
+      "ds_read_b128 %4, %8 offset:%13\n\tds_read_b128 %5, %8 offset:%14\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(xa), "=&v"(xb), "=&v"(st[0]), "=&v"(st[1]), "=&v"(st[2]), "=&v"(st[3])
+      : "v"(t0), "v"(t1), "v"(sp), "i"(OFF), "i"(OFF + 2048), "i"(ST), "i"(ST + 32), "i"(ST + 128), "i"(ST + 160));
+}
+
+// The narrower outputs' operands, one wait.
+__device__ inline void lb_tail_reads(uint32_t t0, uint32_t t1, uint32_t t2, uint32_t t3, uint32_t r0,
+                                     uint32_t r1, uint32_t w, s16x4 (&tr)[4], u32x2& lo, u32x2& hi, f32x4& wf) {
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %7\n\tds_read_b64_tr_b16 %1, %8\n\tds_read_b64_tr_b16 %2, %9\n\t"
+      "ds_read_b64_tr_b16 %3, %10\n\tds_read_b64 %4, %11\n\tds_read_b64 %5, %12\n\t"
+      "ds_read_b128 %6, %13\n\ts_waitcnt lgkmcnt(0)"
+      : "=&v"(tr[0]), "=&v"(tr[1]), "=&v"(tr[2]), "=&v"(tr[3]), "=&v"(lo), "=&v"(hi), "=&v"(wf)
+      : "v"(t0), "v"(t1), "v"(t2), "v"(t3), "v"(r0), "v"(r1), "v"(w));
+}
+
+__device__ inline bf16x8 lb_frag(s16x4 a, s16x4 b) {
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+__device__ inline float lb_dot8(bf16x8 f, float s) {
+  const bf16x2 one2 = {(bf16)1.f, (bf16)1.f};
+  s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(f, f, 0, 1), one2, s, false);
+  s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(f, f, 2, 3), one2, s, false);
+  s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(f, f, 4, 5), one2, s, false);
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(f, f, 6, 7), one2, s, false);
+}
+
+template <int NW, bool FG, bool FD>
+__global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
+  using L = LbL<NW>;
+  constexpr int TPW = L::TPW;
+  __shared__ __align__(16) char slots[L::SLOTS * L::SLOT];
+  __shared__ __align__(16) char wtail[4 * 1024];
+  __shared__ __align__(16) float csum[LB_WAVES][32][2];
+  __shared__ __align__(16) bf16 gam[LNL_K];
+  __shared__ __align__(16) uint32_t ttab[2][64][4];  // tail reads of a lane: transposed (offset, row step), two row quads
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kt = wave & 3, h = wave >> 2;
+  const int tail = a.ncols - 128 * NW;  // columns of the narrower outputs
+
+  // W fragments (rows permuted so that acc[8 a + e] is feature 32 kt + 16 a +
+  // 8 g + e, as in lnl_bwd_dx)
+  const int wrow = 32 * kt + 16 * (l32 >> 4) + 8 * ((l32 >> 2) & 1) + 4 * ((l32 >> 3) & 1) + (l32 & 3);
+  auto w_frag = [&](int n) {  // columns n .. n + 7 (zero past the last)
+    const bf16* p = a.w + (int64_t)wrow * a.ncols + n;
+    const u32x2 lo = n < a.ncols ? *(const u32x2*)p : u32x2{0u, 0u};
+    const u32x2 hi = n + 4 < a.ncols ? *(const u32x2*)(p + 4) : u32x2{0u, 0u};
+    return __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
+  };
+  bf16x8 wr[FD ? TPW : 1][2];
+  if constexpr (FD) {
+#pragma unroll
+    for (int i = 0; i < TPW; ++i)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) wr[i][s] = w_frag(32 * (h + 2 * i) + 16 * s + 8 * g);
+  }
+  if (h == 1) *(bf16x8*)(wtail + kt * 1024 + 16 * lane) = w_frag(128 * NW + 8 * g);  // (h = 0: times zeros)
+  if (tid < LNL_K) gam[tid] = a.gamma[tid];
+  if (tid < 16 * L::SLOTS) *(uint32_t*)(slots + (tid >> 4) * L::SLOT + L::ZERO + 4 * (tid & 15)) = 0u;
+
+  // the narrower outputs: where quad q (columns 128 NW + 4 q ..) is staged
+  int n_tail = a.n_out - NW;
+  auto tail_quad = [&](int q, uint32_t& off, uint32_t& pitch) {
+    off = L::ZERO;
+    pitch = 0;
+    const int col = 128 * NW + 4 * q;
+    for (int i = NW; i < a.n_out; ++i)
+      if (col >= a.start[i] && col < a.start[i + 1]) {
+        pitch = 2u * (uint32_t)(a.start[i + 1] - a.start[i]);
+        off = L::TL + 64u * (uint32_t)(a.start[i] - 128 * NW) + 2u * (uint32_t)(col - a.start[i]);
+      }
+  };
+  const uint32_t base = lds_addr(slots);
+  const int G4 = lane >> 4, jj = lane & 3, pe = ((lane & 15) >> 2) + 4 * (G4 >> 1);
+  // The narrower outputs' tile: the waves with h = 0 sum its G, those with
+  // h = 1 add its part of do1.  All run both, without a branch: the other
+  // waves' rows are zeros, and their G is not stored.
+  if (kt == 0) {
+    uint32_t t, ps, r0, r1, p0, p1;
+    tail_quad(4 * (G4 & 1) + jj, t, ps);  // columns 16 (G4 % 2) + 4 jj of rows pe + 8 j
+    tail_quad(2 * g, r0, p0);             // columns 8 g .. + 7 of row l32
+    tail_quad(2 * g + 1, r1, p1);
+    ttab[h][lane][0] = t + (uint32_t)pe * ps;
+    ttab[h][lane][1] = 8 * ps;
+    ttab[h][lane][2] = h == 1 ? r0 + (uint32_t)l32 * p0 : (uint32_t)L::ZERO;
+    ttab[h][lane][3] = h == 1 ? r1 + (uint32_t)l32 * p1 : (uint32_t)L::ZERO;
+  }
+
+  // DMA: piece `wave` (rows 4 wave .. + 3) of x and of every 128-column
+  // output; waves 0 and 1 the statistics; wave 2 + i narrower output i
+  const uint32_t mb = (uint32_t)a.m;
+  const int ti = NW + wave - 2;  // this wave's narrower output
+  const bool has_tail = wave >= 2 && wave - 2 < n_tail;
+  const uint32_t tw = has_tail ? (uint32_t)(a.start[ti + 1] - a.start[ti]) : 0u;
+  const uint32_t toff = has_tail ? (uint32_t)(L::TL + 64 * (a.start[ti] - 128 * NW)) : 0u;
+  const bf16* tsrc = has_tail ? a.dout[ti] : a.x;
+  const float* ssrc = wave == 0 ? a.mean : a.rstd;
+  const int64_t units = (a.m + 31) / 32;
+  auto issue = [&](int64_t u, int sl, int lane) {
+    const uint32_t lsw = 256u * (lane >> 4) + 16u * ((lane & 15) ^ (4 * (lane >> 4)) ^ (wave & 3)) + 1024u * wave;
+    char* d = slots + sl * L::SLOT;
+    const bool real = u < units;
+    const uint32_t n = real ? mb * 256u : 0u;
+    const uint32_t vo = (uint32_t)u * 8192u + lsw;
+    dma16b(buf_rsrc_n(a.x, n), vo, d + 1024 * wave);
+#pragma unroll
+    for (int o = 0; o < NW; ++o) dma16b(buf_rsrc_n(a.dout[o], n), vo, d + L::DO + 8192 * o + 1024 * wave);
+    if (wave < 2) {
+      if (lane < 8) dma16b(buf_rsrc_n(ssrc, real ? mb * 4u : 0u), (uint32_t)u * 128u + 16u * lane, d + L::ST + 128 * wave);
+    } else if (tw != 0) {
+      if (lane < 4 * (int)tw) dma16b(buf_rsrc_n(tsrc, real ? mb * 2u * tw : 0u), (uint32_t)u * 64u * tw + 16u * lane, d + toff);
+    }
+  };
+
+  // LDS read offsets inside a slot: a transposed read's is vt ^ (64 t ^ 32 o)
+  // for the 32-column piece t of a 256-byte row (rows 8 further on: o = 1,
+  // plus 2048), a row read's vr ^ 16 c for chunk c (its bit 0 is in vr).  Two
+  // registers, opaque to the compiler at every use, stand for the sixteen
+  // addresses of a unit, which would not fit.
+  uint32_t vt = (uint32_t)(pe * 256 + 16 * ((2 * (G4 & 1) + (jj >> 1)) ^ lb_perm(pe)) + 8 * (jj & 1));
+  uint32_t vr = (uint32_t)(l32 * 256 + 16 * (g ^ lb_perm(l32)));
+
+  f32x16 G[FG ? TPW : 1] = {}, Gt = {};
+  float ss0 = 0.f, ss1 = 0.f, sst = 0.f;
+  int64_t u = blockIdx.x;
+  issue(u, 0, lane);
+  issue(u + gridDim.x, 1, lane);
+  // A unit's end waits until at most the operations issued after the next
+  // unit's copies are in flight: the last unit's store, the copies of the
+  // unit after, this unit's store.  (The empty store stands for the last
+  // unit's in the first one.)
+  const int np = 1 + NW + (wave < 2 || tw != 0 ? 1 : 0);
+  if constexpr (FD) __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, buf_rsrc_n(a.dx, 0u), 0, 0, 0);
+  wait_vm_n(np + (FD ? 1 : 0));
+  __syncthreads();
+  int ln = lane;
+  for (int sl = 0; u < units; u += gridDim.x, sl = sl == L::SLOTS - 1 ? 0 : sl + 1) {
+    // (nothing derived from the lane is kept across units: the registers go
+    // to the sums)
+    asm volatile("" : "+v"(ln));
+    const int lane = ln, g = lane >> 5, l32 = lane & 31;
+    issue(u + 2 * (int64_t)gridDim.x, sl == 0 ? L::SLOTS - 1 : sl - 1, lane);
+    const uint32_t bs = base + sl * L::SLOT;
+    // A = xhat^T of the wave's k tile, normalised in registers
+    bf16x8 af[2];
+    auto xhat = [&](auto hc) {  // positions 16 hh .. + 15
+      constexpr int hh = decltype(hc)::value;
+      s16x4 xa, xb;
+      f32x4 st[4];
+      asm volatile("" : "+v"(vt));
+      lb_x_reads<4096 * hh, L::ST + 64 * hh>((vt ^ (64 * kt)) + bs, (vt ^ (64 * kt ^ 32)) + bs, bs + 16 * g, xa, xb, st);
+      const bf16x8 xv = lb_frag(xa, xb);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        af[hh][e] = (bf16)(((float)xv[e] - st[0][e]) * st[2][e]);
+        af[hh][4 + e] = (bf16)(((float)xv[4 + e] - st[1][e]) * st[3][e]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (FG) {
+      xhat(slot_c<0>{});
+      xhat(slot_c<1>{});
+    }
+    f32x16 acc = {};
+    auto tile = [&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      const int q = h + 2 * (i & 1);  // the tile's piece of its output's rows
+      asm volatile("" : "+v"(vt), "+v"(vr));
+      const uint32_t t0 = (vt ^ (64 * q)) + bs, t1 = (vt ^ (64 * q ^ 32)) + bs;
+      const uint32_t r0 = (vr ^ (64 * q)) + bs, r1 = (vr ^ (64 * q ^ 32)) + bs;
+      constexpr int OFF = L::DO + 8192 * (i >> 1);
+      s16x4 tr[4];
+      f32x4 rf[2];
+      if constexpr (FG && FD)
+        lb_tile_reads<OFF>(t0, t1, r0, r1, tr, rf);
+      else if constexpr (FG)
+        tr_read4_wait(t0 + OFF, t1 + OFF + 2048, t0 + OFF + 4096, t1 + OFF + 6144, tr);
+      else
+        lb_row_reads<OFF>(r0, r1, rf);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        if constexpr (FD) acc = Mma<bf16>::mma(wr[i][s], __builtin_bit_cast(bf16x8, rf[s]), acc);
+        if constexpr (FG) G[i] = Mma<bf16>::mma(af[s], tr_frag(tr, s), G[i]);
+      }
+      if constexpr (FG && FD) __builtin_amdgcn_sched_barrier(0);  // one tile's operands at a time (registers)
+    };
+    tile(slot_c<0>{});
+    tile(slot_c<1>{});
+    tile(slot_c<2>{});
+    tile(slot_c<3>{});
+    if constexpr (TPW > 4) {
+      tile(slot_c<4>{});
+      tile(slot_c<5>{});
+    }
+    if constexpr (TPW > 6) {
+      tile(slot_c<6>{});
+      tile(slot_c<7>{});
+    }
+    // column sums: tiles i = kt and kt + 4 (i < TPW) are this wave's
+    if constexpr (FG) {
+      s16x4 r[4];
+      asm volatile("" : "+v"(vt));
+      const int q = h + 2 * (kt & 1);
+      const uint32_t o = bs + L::DO + 8192 * (kt >> 1), t0 = (vt ^ (64 * q)) + o, t1 = (vt ^ (64 * q ^ 32)) + o;
+      if (kt < TPW) {
+        tr_read4_wait(t0, t1 + 2048, t0 + 4096, t1 + 6144, r);
+        ss0 = lb_dot8(tr_frag(r, 1), lb_dot8(tr_frag(r, 0), ss0));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (TPW > 4 && kt + 4 < TPW) {
+        tr_read4_wait(t0 + 16384, t1 + 18432, t0 + 20480, t1 + 22528, r);
+        ss1 = lb_dot8(tr_frag(r, 1), lb_dot8(tr_frag(r, 0), ss1));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    {
+      f32x4 tt, wf;
+      lb_read16<0>(lds_addr(ttab) + 1024 * h + 16 * lane, tt);
+      const uint32_t t = bs + __float_as_uint(tt[0]), ts = __float_as_uint(tt[1]);
+      s16x4 r[4];
+      u32x2 lo, hi;
+      lb_tail_reads(t, t + ts, t + 2 * ts, t + 3 * ts, bs + __float_as_uint(tt[2]), bs + __float_as_uint(tt[3]),
+                    lds_addr(wtail) + kt * 1024 + 16 * lane, r, lo, hi, wf);
+      if constexpr (FG) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) Gt = Mma<bf16>::mma(af[s], tr_frag(r, s), Gt);
+        sst = lb_dot8(tr_frag(r, 1), lb_dot8(tr_frag(r, 0), sst));  // stored by one wave
+      }
+      if constexpr (FD)
+        acc = Mma<bf16>::mma(__builtin_bit_cast(bf16x8, wf),
+                             __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]}), acc);
+    }
+    if constexpr (FD) {
+    // the other half of the k tile's features goes to the partner wave,
+    // through this slot's dO2 (all of whose readers are done)
+    lds_barrier();
+    const uint32_t ex = bs + L::DO + 16 * lane;
+    f32x4 own[2];
+    {
+      f32x4 o[2];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        o[e >> 2][e & 3] = h == 0 ? acc[8 + e] : acc[e];
+        own[e >> 2][e & 3] = h == 0 ? acc[e] : acc[8 + e];
+      }
+      asm volatile("ds_write_b128 %0, %1\n\tds_write_b128 %0, %2 offset:1024\n\ts_waitcnt lgkmcnt(0)" ::"v"(
+                       ex + 2048 * wave),
+                   "v"(o[0]), "v"(o[1])
+                   : "memory");
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    // the partner's part, this lane's x and statistics, gamma
+    f32x4 pr[2], xq, gq;
+    float mean, rstd;
+    asm volatile("" : "+v"(vr));
+    asm volatile(
+        "ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:1024\n\tds_read_b128 %2, %7\n\t"
+        "ds_read_b32 %3, %8 offset:%10\n\tds_read_b32 %4, %8 offset:%11\n\t"
+        "ds_read_b128 %5, %9\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(pr[0]), "=&v"(pr[1]), "=&v"(xq), "=&v"(mean), "=&v"(rstd), "=&v"(gq)
+        : "v"(ex + 2048 * (wave ^ 4)), "v"((vr ^ (64 * kt ^ 32 * h)) + bs), "v"(bs + 4 * l32),
+          "v"(lds_addr(gam) + 2 * (32 * kt + 16 * h + 8 * g)), "i"(L::ST), "i"(L::ST + 128));
+    const bf16x8 gl = __builtin_bit_cast(bf16x8, gq);
+    const bf16x8 xv = __builtin_bit_cast(bf16x8, xq);
+    float wdy[8], xh[8], c1 = 0.f, c2 = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      xh[e] = ((float)xv[e] - mean) * rstd;
+      wdy[e] = (own[e >> 2][e & 3] + pr[e >> 2][e & 3]) * (float)gl[e];
+      c1 = fmaf(xh[e], wdy[e], c1);
+      c2 += wdy[e];
+    }
+    c1 = wave_xor32_sum(c1);
+    c2 = wave_xor32_sum(c2);
+    const uint32_t cs = lds_addr(csum) + 8 * l32;  // both halves of the wave write the same sums
+    asm volatile("ds_write2_b32 %0, %1, %2 offset1:1\n\ts_waitcnt lgkmcnt(0)" ::"v"(cs + 256 * wave), "v"(c1), "v"(c2) : "memory");
+    lds_barrier();
+    f32x2 cw[LB_WAVES];
+    asm volatile(
+        "ds_read_b64 %0, %8\n\tds_read_b64 %1, %8 offset:256\n\tds_read_b64 %2, %8 offset:512\n\t"
+        "ds_read_b64 %3, %8 offset:768\n\tds_read_b64 %4, %8 offset:1024\n\t"
+        "ds_read_b64 %5, %8 offset:1280\n\tds_read_b64 %6, %8 offset:1536\n\t"
+        "ds_read_b64 %7, %8 offset:1792\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(cw[0]), "=&v"(cw[1]), "=&v"(cw[2]), "=&v"(cw[3]), "=&v"(cw[4]), "=&v"(cw[5]),
+          "=&v"(cw[6]), "=&v"(cw[7])
+        : "v"(cs));
+    c1 = 0.f;
+    c2 = 0.f;
+#pragma unroll
+    for (int w = 0; w < LB_WAVES; ++w) {
+      c1 += cw[w][0];
+      c2 += cw[w][1];
+    }
+    c1 *= 1.f / LNL_K;
+    c2 *= 1.f / LNL_K;
+    bf16x8 dx;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) dx[e] = (bf16)(rstd * (wdy[e] - c1 * xh[e] - c2));
+    // every lane stores (rows past m are dropped by the range check)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, dx), buf_rsrc_n(a.dx, mb * 256u),
+                                           (uint32_t)u * 8192u + 256u * l32 + 64u * kt + 32u * h + 16u * g, 0, 0);
+    }
+    wait_vm_n(np + (FD ? 2 : 0));  // the next unit has landed
+    lds_barrier();
+  }
+  wait_vm<0>();  // the copies past the last unit land before the workgroup ends
+  if constexpr (!FG) return;
+  // this workgroup's slab: G rows k, columns of its tiles, and the column sums
+  float* slab = a.gpart + (int64_t)blockIdx.x * (LNL_K + 1) * a.np;
+#pragma unroll
+  for (int i = 0; i < (FG ? TPW : 0); ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      slab[(int64_t)(32 * kt + acc_row(v, g)) * a.np + 32 * (h + 2 * i) + l32] = G[i][v];
+  float* srow = slab + (int64_t)LNL_K * a.np;
+  ss0 = wave_xor32_sum(ss0);
+  ss1 = wave_xor32_sum(ss1);
+  if (g == 0) {
+    if (kt < TPW) srow[32 * (h + 2 * kt) + l32] = ss0;
+    if (kt + 4 < TPW) srow[32 * (h + 2 * (kt + 4)) + l32] = ss1;
+  }
+  if (tail > 0 && h == 0) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      slab[(int64_t)(32 * kt + acc_row(v, g)) * a.np + 128 * NW + l32] = Gt[v];
+    sst = wave_xor32_sum(sst);
+    if (kt == 0 && g == 0) srow[128 * NW + l32] = sst;
+  }
+}
+
 // gsum[r][n] = sum over workgroups p (in order p = c, c + 8, ..., then the 8
 // chains c = 0..7 in order) of gpart[p][r][n]; one workgroup per (row r,
 // 128 columns).
@@ -930,6 +1332,24 @@ size_t lnl_bwd_workspace(int64_t m, int np) {
 
 hipError_t launch_lnl_bwd(const LnlBwdArgs& a, hipStream_t s) {
   const int64_t units = (a.m + 31) / 32;
+  int nw = 0;  // leading outputs of 128 columns
+  while (nw < a.n_out && a.start[nw + 1] - a.start[nw] == 128) ++nw;
+  const bool fused = nw >= 2 && nw <= 4 && a.ncols - 128 * nw <= LB_TAIL && a.n_out - nw <= 6;
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.nwg), dim3(LB_THREADS), 0, s, a); };
+  if (fused && nw == 4) {
+    {
+      KernelTimer t(K_LNL_BWD_DX, s);
+      go(lnl_bwd_kernel<4, false, true>);
+    }
+    KernelTimer t(K_LNL_BWD_G, s);
+    go(lnl_bwd_kernel<4, true, false>);
+  } else if (fused) {
+    KernelTimer t(K_LNL_BWD_DX, s);
+    if (nw == 3)
+      go(lnl_bwd_kernel<3, true, true>);
+    else
+      go(lnl_bwd_kernel<2, true, true>);
+  } else {
   {
     KernelTimer t(K_LNL_BWD_DX, s);
     const int nwg = (int)std::min<int64_t>(256, (units + LBX_WAVES - 1) / LBX_WAVES);
@@ -942,6 +1362,7 @@ hipError_t launch_lnl_bwd(const LnlBwdArgs& a, hipStream_t s) {
   {
     KernelTimer t(K_LNL_BWD_G, s);
     hipLaunchKernelGGL(lnl_bwd_g_kernel, dim3(a.nwg), dim3(64 * LBG_WAVES), 0, s, a);
+  }
   }
   {
     KernelTimer t(K_LNL_REDUCE, s);
