@@ -304,11 +304,15 @@ def cpu_baseline(w, t, target_s, row_range=None, whole=()):
 
 
 def lnl_kernel_bytes(m, cols, k=128):
-    """Algorithmic HBM bytes per launch of the fused projection's main kernels."""
+    """Algorithmic HBM bytes per launch of the fused projection's main kernels.
+
+    With four leading outputs of 128 columns and at most 16 columns after them
+    lnl_bwd_dx sums the first three as well and lnl_bwd_g reads the rest only."""
     n = int(sum(cols))
+    shared = 384 if list(cols[:4]) == [128] * 4 and n <= 528 else 0
     return {"lnl_fwd": m * k * 2 + m * n * 2 + m * 8,
             "lnl_bwd_dx": 2 * m * k * 2 + m * n * 2 + m * 8,
-            "lnl_bwd_g": m * k * 2 + m * n * 2 + m * 8}
+            "lnl_bwd_g": m * k * 2 + m * (n - shared) * 2 + m * 8}
 
 
 def lnl_cpu_baseline(t, target_s):

@@ -869,20 +869,33 @@ __global__ __launch_bounds__(64 * LBG_WAVES) void lnl_bwd_g_kernel(LnlBwdArgs a)
   }
 }
 
-// lnl_bwd: dx and the row sums in one pass over x and dO2, for the shapes of
-// the attention's projection: NW leading outputs of 128 columns (2 to 4) and
-// up to 16 further columns in narrower outputs.  Persistent workgroups of
+// lnl_bwd: dx and row sums from one staged copy of x and dO2, for the shapes
+// of the attention's projection: NW leading outputs of 128 columns (2 to 4)
+// and up to 16 further columns in narrower outputs.  Persistent workgroups of
 // eight waves, one per CU, walk 32-row units; a unit's x, statistics and dO2
-// rows arrive in one of two LDS slots by DMA while the other is worked on.
+// rows arrive by DMA in a ring of three LDS slots, two units ahead.
 // Wave (kt, h) = (w % 4, w / 4) owns features 32 kt .. + 31 and the 32-column
-// tiles T = h + 2 i:
-//   do1^T [32 k][32 rows] += W[k][T] . dO2[rows][T]^T  (partial: its tiles)
-//   G[i]  [32 k][T]       += xhat^T dO2                (kept over all units)
-// Every dO2 tile is read from LDS in both forms, rows and transposed.  The W
-// fragments of its tiles stay with the wave, in registers or (WL tiles) in
-// LDS.  The two partial do1 of a k tile are exchanged half and half through
-// LDS, so that each wave ends with 16 features of 32 rows, 8 consecutive ones
-// per lane; c1 and c2 are summed over the waves through LDS.
+// tiles T = h + 2 i (counted from the first output staged):
+//   G[i]  [32 k][T]       += xhat^T dO2                (i < GT, kept over all units)
+//   do1^T [32 k][32 rows] += W[k][T] . dO2[rows][T]^T  (FD; partial: its tiles)
+// from transposed and row reads of the same staged tile, without a branch; the
+// W fragments of a wave's tiles stay in its registers.  The two partial do1
+// of a k tile are exchanged half and half through LDS, so that each wave
+// finishes 16 features of 32 rows, 8 consecutive ones per lane; c1 and c2 are
+// summed over the waves through LDS.
+//
+// What bounds it, at m = 768^2 and 128,128,128,128,4 columns: the sums of all
+// columns in a pass of their own run at HBM rate (157 us for 765 MB, 4.9 TB/s;
+// lnl_bwd_g, whose tiles hang on branches, 228), and dx alone is issue bound
+// (220 us; lnl_bwd_dx, which reads all of W from LDS again for every 32 rows
+// and wave, 244).  Each 128-column output that dx also sums adds 10 to 13 us
+// to it and takes 25 off the other pass (one, two or three outputs with dx:
+// 574, 555 and 542 us for forward and backward).  Four outputs' sums and W
+// would take 208 of the 256 registers and the compiler then keeps tiles in
+// scratch, which waits for the copies in flight; three fit (240), so the
+// fourth output's sums take a pass over x and that output alone: 353 us for
+// both against 468.  128,128,128 columns: one
+// pass, 225 against 381 us.
 //
 // Slot rows are 256 bytes (one 128-column row of x or of an output), chunk c
 // (8 columns) of row p at chunk slot c ^ (4 (p % 4) + (p / 4) % 4): 16
@@ -892,12 +905,11 @@ __global__ __launch_bounds__(64 * LBG_WAVES) void lnl_bwd_g_kernel(LnlBwdArgs a)
 constexpr int LB_WAVES = 8, LB_THREADS = 64 * LB_WAVES;
 constexpr int LB_TAIL = 16;  // columns past the 128-column outputs, at most
 
-template <int NW>
+template <int NS>  // 128-column outputs staged
 struct LbL {
-  static constexpr int TPW = 2 * NW;              // 32-column tiles per wave
   static constexpr int SLOTS = 3;
   static constexpr int DO = 8192;                 // slot: x, dO2 outputs, mean, rstd, tail, zeros
-  static constexpr int ST = DO + NW * 8192;
+  static constexpr int ST = DO + NS * 8192;
   static constexpr int TL = ST + 256;
   static constexpr int ZERO = TL + 64 * LB_TAIL;
   static constexpr int SLOT = ZERO + 64;
@@ -966,12 +978,17 @@ __device__ inline float lb_dot8(bf16x8 f, float s) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(f, f, 6, 7), one2, s, false);
 }
 
-template <int NW, bool FG, bool FD>
+template <int NW, int G0, int G1, bool FD>
 __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
-  using L = LbL<NW>;
-  constexpr int TPW = L::TPW;
+  constexpr int S0 = FD ? 0 : G0, S1 = FD ? NW : G1;  // outputs staged
+  constexpr int TPW = 2 * (S1 - S0);                  // 32-column tiles per wave: T = 4 S0 + h + 2 i
+  constexpr int GT = 2 * (G1 - G0);                   // tiles i < GT are summed
+  constexpr bool TG = G1 == NW;                       // the narrower outputs are summed too
+  static_assert(G0 == S0 && G1 > G0, "the sums start at the first output staged");
+  using L = LbL<S1 - S0>;
   __shared__ __align__(16) char slots[L::SLOTS * L::SLOT];
   __shared__ __align__(16) char wtail[4 * 1024];
+  __shared__ __align__(16) char exch[FD ? LB_WAVES * 2048 : 16];
   __shared__ __align__(16) float csum[LB_WAVES][32][2];
   __shared__ __align__(16) bf16 gam[LNL_K];
   __shared__ __align__(16) uint32_t ttab[2][64][4];  // tail reads of a lane: transposed (offset, row step), two row quads
@@ -994,9 +1011,9 @@ __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
 #pragma unroll
     for (int i = 0; i < TPW; ++i)
 #pragma unroll
-      for (int s = 0; s < 2; ++s) wr[i][s] = w_frag(32 * (h + 2 * i) + 16 * s + 8 * g);
+      for (int s = 0; s < 2; ++s) wr[i][s] = w_frag(32 * (4 * S0 + h + 2 * i) + 16 * s + 8 * g);
   }
-  if (h == 1) *(bf16x8*)(wtail + kt * 1024 + 16 * lane) = w_frag(128 * NW + 8 * g);  // (h = 0: times zeros)
+  if (h == 1) *(bf16x8*)(wtail + kt * 1024 + 16 * lane) = w_frag(128 * NW + 8 * g);
   if (tid < LNL_K) gam[tid] = a.gamma[tid];
   if (tid < 16 * L::SLOTS) *(uint32_t*)(slots + (tid >> 4) * L::SLOT + L::ZERO + 4 * (tid & 15)) = 0u;
 
@@ -1016,7 +1033,7 @@ __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
   const int G4 = lane >> 4, jj = lane & 3, pe = ((lane & 15) >> 2) + 4 * (G4 >> 1);
   // The narrower outputs' tile: the waves with h = 0 sum its G, those with
   // h = 1 add its part of do1.  All run both, without a branch: the other
-  // waves' rows are zeros, and their G is not stored.
+  // waves' rows and W are zeros, and their G is not stored.
   if (kt == 0) {
     uint32_t t, ps, r0, r1, p0, p1;
     tail_quad(4 * (G4 & 1) + jj, t, ps);  // columns 16 (G4 % 2) + 4 jj of rows pe + 8 j
@@ -1046,7 +1063,7 @@ __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
     const uint32_t vo = (uint32_t)u * 8192u + lsw;
     dma16b(buf_rsrc_n(a.x, n), vo, d + 1024 * wave);
 #pragma unroll
-    for (int o = 0; o < NW; ++o) dma16b(buf_rsrc_n(a.dout[o], n), vo, d + L::DO + 8192 * o + 1024 * wave);
+    for (int o = S0; o < S1; ++o) dma16b(buf_rsrc_n(a.dout[o], n), vo, d + L::DO + 8192 * (o - S0) + 1024 * wave);
     if (wave < 2) {
       if (lane < 8) dma16b(buf_rsrc_n(ssrc, real ? mb * 4u : 0u), (uint32_t)u * 128u + 16u * lane, d + L::ST + 128 * wave);
     } else if (tw != 0) {
@@ -1062,7 +1079,7 @@ __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
   uint32_t vt = (uint32_t)(pe * 256 + 16 * ((2 * (G4 & 1) + (jj >> 1)) ^ lb_perm(pe)) + 8 * (jj & 1));
   uint32_t vr = (uint32_t)(l32 * 256 + 16 * (g ^ lb_perm(l32)));
 
-  f32x16 G[FG ? TPW : 1] = {}, Gt = {};
+  f32x16 G[GT] = {}, Gt = {};
   float ss0 = 0.f, ss1 = 0.f, sst = 0.f;
   int64_t u = blockIdx.x;
   issue(u, 0, lane);
@@ -1071,17 +1088,83 @@ __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
   // unit's copies are in flight: the last unit's store, the copies of the
   // unit after, this unit's store.  (The empty store stands for the last
   // unit's in the first one.)
-  const int np = 1 + NW + (wave < 2 || tw != 0 ? 1 : 0);
+  const int np = 1 + S1 - S0 + (wave < 2 || tw != 0 ? 1 : 0);
   if constexpr (FD) __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, buf_rsrc_n(a.dx, 0u), 0, 0, 0);
   wait_vm_n(np + (FD ? 1 : 0));
   __syncthreads();
+  // dx of a unit is finished a unit later: its parts are exchanged at the end
+  // of its own loop, the row sums c1 and c2 formed at the start of the next
+  // (dx_sums) and dx stored in the middle of it (dx_store), so that two
+  // barriers per unit serve and neither their waits nor the reads between
+  // them stand on their own.
+  f32x4 own[2] = {};
+  float wdy[8], xh[8], rstd = 0.f;
+  auto dx_sums = [&](uint32_t bs, int g, int l32, int lane) {
+    // the partner's part, this lane's x and statistics, gamma
+    f32x4 pr[2], xq, gq;
+    float mean;
+    asm volatile("" : "+v"(vr));
+    asm volatile(
+        "ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:1024\n\tds_read_b128 %2, %7\n\t"
+        "ds_read_b32 %3, %8 offset:%10\n\tds_read_b32 %4, %8 offset:%11\n\t"
+        "ds_read_b128 %5, %9\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(pr[0]), "=&v"(pr[1]), "=&v"(xq), "=&v"(mean), "=&v"(rstd), "=&v"(gq)
+        : "v"(lds_addr(exch) + 2048 * (wave ^ 4) + 16 * lane), "v"((vr ^ (64 * kt ^ 32 * h)) + bs),
+          "v"(bs + 4 * l32), "v"(lds_addr(gam) + 2 * (32 * kt + 16 * h + 8 * g)), "i"(L::ST),
+          "i"(L::ST + 128));
+    const bf16x8 gl = __builtin_bit_cast(bf16x8, gq), xv = __builtin_bit_cast(bf16x8, xq);
+    float c1 = 0.f, c2 = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      xh[e] = ((float)xv[e] - mean) * rstd;
+      wdy[e] = (own[e >> 2][e & 3] + pr[e >> 2][e & 3]) * (float)gl[e];
+      c1 = fmaf(xh[e], wdy[e], c1);
+      c2 += wdy[e];
+    }
+    c1 = wave_xor32_sum(c1);
+    c2 = wave_xor32_sum(c2);
+    // (both halves of the wave write the same sums)
+    asm volatile("ds_write2_b32 %0, %1, %2 offset1:1\n\ts_waitcnt lgkmcnt(0)" ::"v"(
+                     lds_addr(csum) + 8 * l32 + 256 * wave),
+                 "v"(c1), "v"(c2)
+                 : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto dx_store = [&](int64_t u, uint32_t nrec, int g, int l32) {
+    f32x2 cw[LB_WAVES];
+    asm volatile(
+        "ds_read_b64 %0, %8\n\tds_read_b64 %1, %8 offset:256\n\tds_read_b64 %2, %8 offset:512\n\t"
+        "ds_read_b64 %3, %8 offset:768\n\tds_read_b64 %4, %8 offset:1024\n\t"
+        "ds_read_b64 %5, %8 offset:1280\n\tds_read_b64 %6, %8 offset:1536\n\t"
+        "ds_read_b64 %7, %8 offset:1792\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(cw[0]), "=&v"(cw[1]), "=&v"(cw[2]), "=&v"(cw[3]), "=&v"(cw[4]), "=&v"(cw[5]),
+          "=&v"(cw[6]), "=&v"(cw[7])
+        : "v"(lds_addr(csum) + 8 * l32));
+    float c1 = 0.f, c2 = 0.f;
+#pragma unroll
+    for (int w = 0; w < LB_WAVES; ++w) {
+      c1 += cw[w][0];
+      c2 += cw[w][1];
+    }
+    c1 *= 1.f / LNL_K;
+    c2 *= 1.f / LNL_K;
+    bf16x8 dx;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) dx[e] = (bf16)(rstd * (wdy[e] - c1 * xh[e] - c2));
+    // every lane stores (rows past m are dropped by the range check)
+    __builtin_amdgcn_raw_buffer_store_b128(
+        __builtin_bit_cast(u32x4, dx), buf_rsrc_n(a.dx, nrec),
+        (uint32_t)u * 8192u + 256u * l32 + 64u * kt + 32u * h + 16u * g, 0, 0);
+  };
   int ln = lane;
   for (int sl = 0; u < units; u += gridDim.x, sl = sl == L::SLOTS - 1 ? 0 : sl + 1) {
     // (nothing derived from the lane is kept across units: the registers go
     // to the sums)
     asm volatile("" : "+v"(ln));
     const int lane = ln, g = lane >> 5, l32 = lane & 31;
-    issue(u + 2 * (int64_t)gridDim.x, sl == 0 ? L::SLOTS - 1 : sl - 1, lane);
+    const int slp = sl == 0 ? L::SLOTS - 1 : sl - 1;  // the last unit's slot, the next but one's
+    if constexpr (!FD) issue(u + 2 * (int64_t)gridDim.x, slp, lane);
+    if constexpr (FD) dx_sums(base + slp * L::SLOT, g, l32, lane);
     const uint32_t bs = base + sl * L::SLOT;
     // A = xhat^T of the wave's k tile, normalised in registers
     bf16x8 af[2];
@@ -1099,10 +1182,8 @@ __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
       }
       __builtin_amdgcn_sched_barrier(0);
     };
-    if constexpr (FG) {
-      xhat(slot_c<0>{});
-      xhat(slot_c<1>{});
-    }
+    xhat(slot_c<0>{});
+    xhat(slot_c<1>{});
     f32x16 acc = {};
     auto tile = [&](auto ic) {
       constexpr int i = decltype(ic)::value;
@@ -1113,23 +1194,25 @@ __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
       constexpr int OFF = L::DO + 8192 * (i >> 1);
       s16x4 tr[4];
       f32x4 rf[2];
-      if constexpr (FG && FD)
+      if constexpr (i < GT && FD)
         lb_tile_reads<OFF>(t0, t1, r0, r1, tr, rf);
-      else if constexpr (FG)
+      else if constexpr (i < GT)
         tr_read4_wait(t0 + OFF, t1 + OFF + 2048, t0 + OFF + 4096, t1 + OFF + 6144, tr);
       else
         lb_row_reads<OFF>(r0, r1, rf);
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         if constexpr (FD) acc = Mma<bf16>::mma(wr[i][s], __builtin_bit_cast(bf16x8, rf[s]), acc);
-        if constexpr (FG) G[i] = Mma<bf16>::mma(af[s], tr_frag(tr, s), G[i]);
+        if constexpr (i < GT) G[i] = Mma<bf16>::mma(af[s], tr_frag(tr, s), G[i]);
       }
-      if constexpr (FG && FD) __builtin_amdgcn_sched_barrier(0);  // one tile's operands at a time (registers)
+      if constexpr (FD) __builtin_amdgcn_sched_barrier(0);  // one tile's operands at a time (registers)
     };
     tile(slot_c<0>{});
     tile(slot_c<1>{});
-    tile(slot_c<2>{});
-    tile(slot_c<3>{});
+    if constexpr (TPW > 2) {
+      tile(slot_c<2>{});
+      tile(slot_c<3>{});
+    }
     if constexpr (TPW > 4) {
       tile(slot_c<4>{});
       tile(slot_c<5>{});
@@ -1138,32 +1221,32 @@ __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
       tile(slot_c<6>{});
       tile(slot_c<7>{});
     }
-    // column sums: tiles i = kt and kt + 4 (i < TPW) are this wave's
-    if constexpr (FG) {
+    // column sums: tiles i = kt and kt + 4 (i < GT) are this wave's
+    {
       s16x4 r[4];
       asm volatile("" : "+v"(vt));
       const int q = h + 2 * (kt & 1);
       const uint32_t o = bs + L::DO + 8192 * (kt >> 1), t0 = (vt ^ (64 * q)) + o, t1 = (vt ^ (64 * q ^ 32)) + o;
-      if (kt < TPW) {
+      if (kt < GT) {
         tr_read4_wait(t0, t1 + 2048, t0 + 4096, t1 + 6144, r);
         ss0 = lb_dot8(tr_frag(r, 1), lb_dot8(tr_frag(r, 0), ss0));
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (TPW > 4 && kt + 4 < TPW) {
+      if (GT > 4 && kt + 4 < GT) {
         tr_read4_wait(t0 + 16384, t1 + 18432, t0 + 20480, t1 + 22528, r);
         ss1 = lb_dot8(tr_frag(r, 1), lb_dot8(tr_frag(r, 0), ss1));
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    {
+    if constexpr (TG || FD) {
       f32x4 tt, wf;
       lb_read16<0>(lds_addr(ttab) + 1024 * h + 16 * lane, tt);
       const uint32_t t = bs + __float_as_uint(tt[0]), ts = __float_as_uint(tt[1]);
       s16x4 r[4];
       u32x2 lo, hi;
       lb_tail_reads(t, t + ts, t + 2 * ts, t + 3 * ts, bs + __float_as_uint(tt[2]), bs + __float_as_uint(tt[3]),
-                    lds_addr(wtail) + kt * 1024 + 16 * lane, r, lo, hi, wf);
-      if constexpr (FG) {
+                    h == 1 ? lds_addr(wtail) + kt * 1024 + 16 * lane : bs + L::ZERO, r, lo, hi, wf);
+      if constexpr (TG) {
 #pragma unroll
         for (int s = 0; s < 2; ++s) Gt = Mma<bf16>::mma(af[s], tr_frag(r, s), Gt);
         sst = lb_dot8(tr_frag(r, 1), lb_dot8(tr_frag(r, 0), sst));  // stored by one wave
@@ -1173,12 +1256,11 @@ __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
                              __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]}), acc);
     }
     if constexpr (FD) {
-    // the other half of the k tile's features goes to the partner wave,
-    // through this slot's dO2 (all of whose readers are done)
-    lds_barrier();
-    const uint32_t ex = bs + L::DO + 16 * lane;
-    f32x4 own[2];
-    {
+      __builtin_amdgcn_sched_barrier(0);
+      lds_barrier();  // csum of the last unit is complete, its slot and the exchange are free
+      issue(u + 2 * (int64_t)gridDim.x, slp, lane);
+      dx_store(u - (int64_t)gridDim.x, u == blockIdx.x ? 0u : mb * 256u, g, l32);
+      // the half of the k tile's features that the partner wave finishes
       f32x4 o[2];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -1186,83 +1268,35 @@ __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
         own[e >> 2][e & 3] = h == 0 ? acc[e] : acc[8 + e];
       }
       asm volatile("ds_write_b128 %0, %1\n\tds_write_b128 %0, %2 offset:1024\n\ts_waitcnt lgkmcnt(0)" ::"v"(
-                       ex + 2048 * wave),
+                       lds_addr(exch) + 2048 * wave + 16 * lane),
                    "v"(o[0]), "v"(o[1])
                    : "memory");
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    lds_barrier();
-    // the partner's part, this lane's x and statistics, gamma
-    f32x4 pr[2], xq, gq;
-    float mean, rstd;
-    asm volatile("" : "+v"(vr));
-    asm volatile(
-        "ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:1024\n\tds_read_b128 %2, %7\n\t"
-        "ds_read_b32 %3, %8 offset:%10\n\tds_read_b32 %4, %8 offset:%11\n\t"
-        "ds_read_b128 %5, %9\n\ts_waitcnt lgkmcnt(0)"
-        : "=&v"(pr[0]), "=&v"(pr[1]), "=&v"(xq), "=&v"(mean), "=&v"(rstd), "=&v"(gq)
-        : "v"(ex + 2048 * (wave ^ 4)), "v"((vr ^ (64 * kt ^ 32 * h)) + bs), "v"(bs + 4 * l32),
-          "v"(lds_addr(gam) + 2 * (32 * kt + 16 * h + 8 * g)), "i"(L::ST), "i"(L::ST + 128));
-    const bf16x8 gl = __builtin_bit_cast(bf16x8, gq);
-    const bf16x8 xv = __builtin_bit_cast(bf16x8, xq);
-    float wdy[8], xh[8], c1 = 0.f, c2 = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      xh[e] = ((float)xv[e] - mean) * rstd;
-      wdy[e] = (own[e >> 2][e & 3] + pr[e >> 2][e & 3]) * (float)gl[e];
-      c1 = fmaf(xh[e], wdy[e], c1);
-      c2 += wdy[e];
-    }
-    c1 = wave_xor32_sum(c1);
-    c2 = wave_xor32_sum(c2);
-    const uint32_t cs = lds_addr(csum) + 8 * l32;  // both halves of the wave write the same sums
-    asm volatile("ds_write2_b32 %0, %1, %2 offset1:1\n\ts_waitcnt lgkmcnt(0)" ::"v"(cs + 256 * wave), "v"(c1), "v"(c2) : "memory");
-    lds_barrier();
-    f32x2 cw[LB_WAVES];
-    asm volatile(
-        "ds_read_b64 %0, %8\n\tds_read_b64 %1, %8 offset:256\n\tds_read_b64 %2, %8 offset:512\n\t"
-        "ds_read_b64 %3, %8 offset:768\n\tds_read_b64 %4, %8 offset:1024\n\t"
-        "ds_read_b64 %5, %8 offset:1280\n\tds_read_b64 %6, %8 offset:1536\n\t"
-        "ds_read_b64 %7, %8 offset:1792\n\ts_waitcnt lgkmcnt(0)"
-        : "=&v"(cw[0]), "=&v"(cw[1]), "=&v"(cw[2]), "=&v"(cw[3]), "=&v"(cw[4]), "=&v"(cw[5]),
-          "=&v"(cw[6]), "=&v"(cw[7])
-        : "v"(cs));
-    c1 = 0.f;
-    c2 = 0.f;
-#pragma unroll
-    for (int w = 0; w < LB_WAVES; ++w) {
-      c1 += cw[w][0];
-      c2 += cw[w][1];
-    }
-    c1 *= 1.f / LNL_K;
-    c2 *= 1.f / LNL_K;
-    bf16x8 dx;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) dx[e] = (bf16)(rstd * (wdy[e] - c1 * xh[e] - c2));
-    // every lane stores (rows past m are dropped by the range check)
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, dx), buf_rsrc_n(a.dx, mb * 256u),
-                                           (uint32_t)u * 8192u + 256u * l32 + 64u * kt + 32u * h + 16u * g, 0, 0);
     }
     wait_vm_n(np + (FD ? 2 : 0));  // the next unit has landed
     lds_barrier();
   }
+  if constexpr (FD) {  // the last unit's dx (its slot is the last one worked on)
+    const int slp = (int)(((units - 1 - blockIdx.x) / gridDim.x) % L::SLOTS);
+    dx_sums(base + slp * L::SLOT, g, l32, lane);
+    lds_barrier();
+    dx_store(u - (int64_t)gridDim.x, mb * 256u, g, l32);
+  }
   wait_vm<0>();  // the copies past the last unit land before the workgroup ends
-  if constexpr (!FG) return;
   // this workgroup's slab: G rows k, columns of its tiles, and the column sums
   float* slab = a.gpart + (int64_t)blockIdx.x * (LNL_K + 1) * a.np;
 #pragma unroll
-  for (int i = 0; i < (FG ? TPW : 0); ++i)
+  for (int i = 0; i < GT; ++i)
 #pragma unroll
     for (int v = 0; v < 16; ++v)
-      slab[(int64_t)(32 * kt + acc_row(v, g)) * a.np + 32 * (h + 2 * i) + l32] = G[i][v];
+      slab[(int64_t)(32 * kt + acc_row(v, g)) * a.np + 32 * (4 * S0 + h + 2 * i) + l32] = G[i][v];
   float* srow = slab + (int64_t)LNL_K * a.np;
   ss0 = wave_xor32_sum(ss0);
   ss1 = wave_xor32_sum(ss1);
   if (g == 0) {
-    if (kt < TPW) srow[32 * (h + 2 * kt) + l32] = ss0;
-    if (kt + 4 < TPW) srow[32 * (h + 2 * (kt + 4)) + l32] = ss1;
+    if (kt < GT) srow[32 * (4 * S0 + h + 2 * kt) + l32] = ss0;
+    if (kt + 4 < GT) srow[32 * (4 * S0 + h + 2 * (kt + 4)) + l32] = ss1;
   }
-  if (tail > 0 && h == 0) {
+  if (TG && tail > 0 && h == 0) {
 #pragma unroll
     for (int v = 0; v < 16; ++v)
       slab[(int64_t)(32 * kt + acc_row(v, g)) * a.np + 128 * NW + l32] = Gt[v];
@@ -1273,13 +1307,16 @@ __global__ __launch_bounds__(LB_THREADS, 1) void lnl_bwd_kernel(LnlBwdArgs a) {
 
 // gsum[r][n] = sum over workgroups p (in order p = c, c + 8, ..., then the 8
 // chains c = 0..7 in order) of gpart[p][r][n]; one workgroup per (row r,
-// 128 columns).
+// 128 columns).  The slabs of the last launch are still in the caches: 15 us
+// for 256 slabs of 129 x 544, and 22 when the larger part of their columns
+// was written a launch earlier (with one load in flight per thread, too).
 __global__ __launch_bounds__(256) void lnl_reduce_kernel(LnlBwdArgs a) {
   __shared__ f32x4 red[8][32];
   const int r = blockIdx.y, t = threadIdx.x, n4 = t & 31, c = t >> 5;
   const int n = blockIdx.x * 128 + 4 * n4;
   f32x4 s = {};
   if (n < a.np)
+#pragma unroll 8
     for (int p = c; p < a.nwg; p += 8)
       s += *(const f32x4*)(a.gpart + ((int64_t)p * (LNL_K + 1) + r) * a.np + n);
   red[c][n4] = s;
@@ -1332,37 +1369,40 @@ size_t lnl_bwd_workspace(int64_t m, int np) {
 
 hipError_t launch_lnl_bwd(const LnlBwdArgs& a, hipStream_t s) {
   const int64_t units = (a.m + 31) / 32;
-  int nw = 0;  // leading outputs of 128 columns
+  // The one-pass kernels take 2 to 4 leading outputs of 128 columns and up to
+  // LB_TAIL columns after them, in at most six outputs (one per wave that
+  // copies no statistics); anything else goes through lnl_bwd_dx and lnl_bwd_g.
+  int nw = 0;
   while (nw < a.n_out && a.start[nw + 1] - a.start[nw] == 128) ++nw;
   const bool fused = nw >= 2 && nw <= 4 && a.ncols - 128 * nw <= LB_TAIL && a.n_out - nw <= 6;
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.nwg), dim3(LB_THREADS), 0, s, a); };
   if (fused && nw == 4) {
-    {
-      KernelTimer t(K_LNL_BWD_DX, s);
-      go(lnl_bwd_kernel<4, false, true>);
+    {  // the smaller part of the slabs first: the larger is still cached when it is reduced
+      KernelTimer t(K_LNL_BWD_G, s);
+      go(lnl_bwd_kernel<4, 3, 4, false>);
     }
-    KernelTimer t(K_LNL_BWD_G, s);
-    go(lnl_bwd_kernel<4, true, false>);
+    KernelTimer t(K_LNL_BWD_DX, s);
+    go(lnl_bwd_kernel<4, 0, 3, true>);
   } else if (fused) {
     KernelTimer t(K_LNL_BWD_DX, s);
     if (nw == 3)
-      go(lnl_bwd_kernel<3, true, true>);
+      go(lnl_bwd_kernel<3, 0, 3, true>);
     else
-      go(lnl_bwd_kernel<2, true, true>);
+      go(lnl_bwd_kernel<2, 0, 2, true>);
   } else {
-  {
-    KernelTimer t(K_LNL_BWD_DX, s);
-    const int nwg = (int)std::min<int64_t>(256, (units + LBX_WAVES - 1) / LBX_WAVES);
-    const int nf = lbx_fast_steps(a);
-    if (nf >= LBX_AHEAD && lbx_steps(a) - nf <= LBX_SLOW_AHEAD)
-      hipLaunchKernelGGL(lnl_bwd_dx_kernel<true>, dim3(nwg), dim3(64 * LBX_WAVES), 0, s, a, nf);
-    else
-      hipLaunchKernelGGL(lnl_bwd_dx_kernel<false>, dim3(nwg), dim3(64 * LBX_WAVES), 0, s, a, nf);
-  }
-  {
-    KernelTimer t(K_LNL_BWD_G, s);
-    hipLaunchKernelGGL(lnl_bwd_g_kernel, dim3(a.nwg), dim3(64 * LBG_WAVES), 0, s, a);
-  }
+    {
+      KernelTimer t(K_LNL_BWD_DX, s);
+      const int nwg = (int)std::min<int64_t>(256, (units + LBX_WAVES - 1) / LBX_WAVES);
+      const int nf = lbx_fast_steps(a);
+      if (nf >= LBX_AHEAD && lbx_steps(a) - nf <= LBX_SLOW_AHEAD)
+        hipLaunchKernelGGL(lnl_bwd_dx_kernel<true>, dim3(nwg), dim3(64 * LBX_WAVES), 0, s, a, nf);
+      else
+        hipLaunchKernelGGL(lnl_bwd_dx_kernel<false>, dim3(nwg), dim3(64 * LBX_WAVES), 0, s, a, nf);
+    }
+    {
+      KernelTimer t(K_LNL_BWD_G, s);
+      hipLaunchKernelGGL(lnl_bwd_g_kernel, dim3(a.nwg), dim3(64 * LBG_WAVES), 0, s, a);
+    }
   }
   {
     KernelTimer t(K_LNL_REDUCE, s);
