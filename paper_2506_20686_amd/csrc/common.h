@@ -162,44 +162,12 @@ __device__ inline float max16(const f32x16& s) {
   return fmaxf(m, s[15]);
 }
 
-// Maximum of 32 values (two accumulators) as a tree of 3-input maxes: 16
-// instructions, depth 4.
-__device__ inline float max3f(float a, float b, float c) { return fmaxf(a, fmaxf(b, c)); }
-__device__ inline float max32(const f32x16& a, const f32x16& b) {
-  float t[12];
-#pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    t[i] = max3f(a[3 * i], a[3 * i + 1], a[3 * i + 2]);
-    t[5 + i] = max3f(b[3 * i], b[3 * i + 1], b[3 * i + 2]);
-  }
-  t[10] = a[15];
-  t[11] = b[15];
-  const float u0 = max3f(t[0], t[1], t[2]), u1 = max3f(t[3], t[4], t[5]);
-  const float u2 = max3f(t[6], t[7], t[8]), u3 = max3f(t[9], t[10], t[11]);
-  return fmaxf(max3f(u0, u1, u2), u3);
-}
 // Tree sum of the 16 entries of a lane.
 __device__ inline float sum16(const f32x16& a) {
   float t[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) t[i] = (a[4 * i] + a[4 * i + 1]) + (a[4 * i + 2] + a[4 * i + 3]);
   return (t[0] + t[1]) + (t[2] + t[3]);
-}
-
-// A-operand that sums a B operand's contraction slots into accumulator row 0:
-// row 0 is all ones, the other rows are zero.  D += ones_row0 * B then adds
-// sum_k B[k][n] to register 0 of the lanes of half g = 0 (row 0), and leaves
-// the other rows at zero.  Moves a per-lane row sum from the VALU to the MFMA.
-template <typename F>
-__device__ inline F ones_row0(int l32);
-template <>
-__device__ inline bf16x8 ones_row0<bf16x8>(int l32) {
-  const bf16 v = l32 == 0 ? (bf16)1.f : (bf16)0.f;
-  return bf16x8{v, v, v, v, v, v, v, v};
-}
-template <>
-__device__ inline float ones_row0<float>(int l32) {
-  return l32 == 0 ? 1.f : 0.f;
 }
 
 // Hardware reciprocal (about 1 ulp), for normalisation and the sigmoid.

@@ -92,18 +92,22 @@ __device__ inline void to_sample(FwdArgs<T>& a) {
   a.lse = at_sample(a.lse, G.bBias);
 }
 
-// Online-softmax state of one (row, 32 queries) pair of a wave.  The row
-// sums of P accumulate on the MFMA: register 0 of the lanes of half 0 of
-// `l` holds sum_k P for the lane's query (see ones_row0).
+// Online-softmax state of one (row, 32 queries) pair of a wave.  `l` is the
+// lane's part of sum_k P for its query (the other half of the wave holds the
+// other keys').
 template <int D>
 struct SoftmaxState {
-  float m;
-  f32x16 l;
+  float m, l;
   f32x16 o[D / 32];  // O^T accumulators (32 channels each): registers <-> channels, lane <-> query
 };
 
 // Forward with register-staged operand blocks (stage.h), for D = 32 or 64
-// channels per head.
+// channels per head.  The fp32 matrix rate bounds it (a 32x32 tile of 32
+// channels is 32 MFMAs of 64 cycles), so the row sums of P are vector adds:
+// on the matrix cores they were 16 more MFMAs per tile.  With one pair of
+// bias tiles in registers (162 -> 128) it runs four waves per SIMD.
+// 193 x 193 pairs, 4 heads of 32 channels: 88 -> 64 us (69 with the row sums
+// alone); 384: 377 -> 288 us; 300, 64 channels: 415 -> 352 us.
 template <typename T, int D>
 __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs<T> a) {
   to_sample(a);
@@ -142,7 +146,7 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs<T> a) {
     else
       zero_frags(qf[i]);
     st[i].m = M_FLOOR;
-    st[i].l = f32x16{};
+    st[i].l = 0.f;
 #pragma unroll
     for (int c = 0; c < NO; ++c) st[i].o[c] = f32x16{};
   }
@@ -159,13 +163,11 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs<T> a) {
     bb[0] = block_bits(kb[0], G.nkt, b);
     if constexpr (FWD_ROWS > 1) bb[1] = row1 ? block_bits(kb[1], G.nkt, b) : 0ull;
   };
-  const typename M::frag ones = ones_row0<typename M::frag>(l32);
-
   // raise the running max to include mx (log2 units) and rescale the state
   auto rescale = [&](SoftmaxState<D>& S, float mx) {
     const float mnew = fmaxf(S.m, mx);
     const float alpha = __builtin_amdgcn_exp2f(S.m - mnew);
-    S.l[0] *= alpha;  // rows 1..31 of l stay zero
+    S.l *= alpha;
 #pragma unroll
     for (int c = 0; c < NO; ++c)
 #pragma unroll
@@ -186,6 +188,7 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs<T> a) {
     if (__any(mx > S.m + STALE_MAX_SLACK)) rescale(S, mx);
 #pragma unroll
     for (int v = 0; v < 16; ++v) s[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[v], c1, -S.m));
+    S.l += sum16(s);
     typename M::frag pf[M::PCH], vf[M::PCH];
     acc_frags(s, pf);
 #pragma unroll
@@ -193,55 +196,6 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs<T> a) {
       quad_frags(vtb + (32 * c + l32) * LDS_TROW + 32 * u, g, vf);
 #pragma unroll
       for (int t = 0; t < M::PCH; ++t) S.o[c] = M::mma(vf[t], pf[t], S.o[c]);  // O^T += V^T P^T
-    }
-#pragma unroll
-    for (int t = 0; t < M::PCH; ++t) S.l = M::mma(ones, pf[t], S.l);  // row sums of P
-  };
-
-  // A full 64-key block (every key valid in both rows): one straight-line
-  // stretch -- all logit MFMAs, then the maxes, one (rare) rescale per row,
-  // then exp / sums / bf16 packing interleaved with the P V MFMAs -- so the
-  // scheduler can overlap the two rows' and sub-tiles' independent work.
-  auto full_block = [&](int buf, const f32x16& c0, const f32x16& c1b) {
-    f32x16 s[FWD_ROWS][2];
-#pragma unroll
-    for (int i = 0; i < FWD_ROWS; ++i) {
-      const T* ksb = ks + (buf * FWD_ROWS + i) * TL::ROWT;
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        typename M::frag kf[KCH];
-        row_frags(ksb + (32 * u + l32) * TL::ROW, g, kf);
-        s[i][u] = M::mma(kf[0], qf[i][0], u ? c1b : c0);
-#pragma unroll
-        for (int t = 1; t < KCH; ++t) s[i][u] = M::mma(kf[t], qf[i][t], s[i][u]);
-      }
-    }
-    float mx[FWD_ROWS];
-#pragma unroll
-    for (int i = 0; i < FWD_ROWS; ++i) mx[i] = wave_xor32_max(max32(s[i][0], s[i][1])) * c1;
-#pragma unroll
-    for (int i = 0; i < FWD_ROWS; ++i)
-      if (__any(mx[i] > st[i].m + STALE_MAX_SLACK)) rescale(st[i], mx[i]);
-#pragma unroll
-    for (int i = 0; i < FWD_ROWS; ++i) {
-      SoftmaxState<D>& S = st[i];
-      const T* vtb = vt + (buf * FWD_ROWS + i) * TL::TRANS;
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          s[i][u][v] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i][u][v], c1, -S.m));
-        typename M::frag pf[M::PCH], vf[M::PCH];
-        acc_frags(s[i][u], pf);
-#pragma unroll
-        for (int c = 0; c < NO; ++c) {
-          quad_frags(vtb + (32 * c + l32) * LDS_TROW + 32 * u, g, vf);
-#pragma unroll
-          for (int t = 0; t < M::PCH; ++t) S.o[c] = M::mma(vf[t], pf[t], S.o[c]);
-        }
-#pragma unroll
-        for (int t = 0; t < M::PCH; ++t) S.l = M::mma(ones, pf[t], S.l);
-      }
     }
   };
 
@@ -276,22 +230,16 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs<T> a) {
   uint64_t bb[FWD_ROWS];
   bits_of(0, bb);
   stage_load(0);
-  f32x16 bA0 = bias_tile(0), bA1 = bias_tile(1), bB0, bB1;
+  f32x16 c0 = bias_tile(0), c1b = bias_tile(1);
   stage_store(0, bb);
   __syncthreads();
-  auto step = [&](int b, const f32x16& c0, const f32x16& c1b, f32x16& n0, f32x16& n1) {
+  for (int b = 0; b < nblk; ++b) {
     const int bn = min(b + 1, nblk - 1);
     uint64_t bbn[FWD_ROWS];
     bits_of(bn, bbn);
     stage_load(bn);
-    n0 = bias_tile(2 * bn);
-    n1 = bias_tile(2 * bn + 1);
     const int buf = b & 1;
-    bool full = bb[0] == ~0ull;
-    if constexpr (FWD_ROWS > 1) full = full && (!row1 || bb[1] == ~0ull);
-    if (active && full) {
-      full_block(buf, c0, c1b);
-    } else if (active) {
+    if (active) {
 #pragma unroll
       for (int i = 0; i < FWD_ROWS; ++i) {
         const T* ksb = ks + (buf * FWD_ROWS + i) * TL::ROWT;
@@ -302,14 +250,15 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs<T> a) {
       }
     }
     if (b + 1 < nblk) stage_store(buf ^ 1, bbn);
+    // (after this block's tiles, not before: one pair of bias tiles in
+    // registers lets four waves run per SIMD)
+    __builtin_amdgcn_sched_barrier(0);
+    c0 = bias_tile(2 * bn);
+    c1b = bias_tile(2 * bn + 1);
+    __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < FWD_ROWS; ++i) bb[i] = bbn[i];
-  };
-  for (int b = 0; b < nblk; b += 2) {
-    step(b, bA0, bA1, bB0, bB1);
-    if (b + 1 >= nblk) break;
-    step(b + 1, bB0, bB1, bA0, bA1);
   }
   if (!active || !qok) return;
 
@@ -318,7 +267,7 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs<T> a) {
   for (int i = 0; i < FWD_ROWS; ++i) {
     if (i == 1 && !row1) break;
     const SoftmaxState<D>& S = st[i];
-    const float lt = wave_xor32_sum(S.l[0]);  // half 1 holds zeros in register 0
+    const float lt = wave_xor32_sum(S.l);
     const float inv = lt > 0.f ? fast_rcp(lt) : 0.f;
     const int64_t base = rowbase[i] + (int64_t)q * G.sPos;
     f32x4 gv[NO][4];  // every gate load before the first store
