@@ -345,6 +345,12 @@ _DTYPES = {torch.float32: F32, torch.bfloat16: BF16}
 
 
 def _check(name, t, shape, dtype, device):
+    # what a good call passes, in one expression (a third less time than the
+    # tests one by one, which name the fault): up to eight tensors a call,
+    # where the smallest calls' kernels take 20 to 45 us in all
+    if (isinstance(t, torch.Tensor) and t.shape == shape and t.dtype is dtype
+            and t.device == device and device.type == "cuda" and t.is_contiguous()):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device != device or t.device.type != "cuda":
@@ -369,9 +375,12 @@ def _common(q, k, v, g, bias, mask):
     if q.dtype not in _DTYPES:
         raise ValueError(f"unsupported dtype {q.dtype}")
     dev = q.device
-    for name, t in (("q", q), ("k", k), ("v", v), ("g", g)):
-        _check(name, t, lead + (n, n, h, d), q.dtype, dev)
-    _check("bias", bias, lead + (n, n, h), q.dtype, dev)
+    shape, dtype = q.shape, q.dtype
+    _check("q", q, shape, dtype, dev)
+    _check("k", k, shape, dtype, dev)
+    _check("v", v, shape, dtype, dev)
+    _check("g", g, shape, dtype, dev)
+    _check("bias", bias, lead + (n, n, h), dtype, dev)
     if mask is not None:
         _check("mask", mask, lead + (n, n), torch.uint8, dev)
     return lead, n, h, d, _DTYPES[q.dtype], dev
@@ -382,7 +391,10 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(dev):
-    return torch.cuda.current_stream(dev).cuda_stream
+    # the handle alone: 0.1 us, against 2 us for the stream object around it
+    if dev.index is None:
+        return torch.cuda.current_stream(dev).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(dev.index)
 
 
 # The torch wrappers give a batch one workspace copy per sample (one launch per
@@ -454,11 +466,11 @@ def bwd(q, k, v, g, bias, out, lse, dout, mask=None, node: int = STARTING,
     """Triangle attention backward.  Returns (dq, dk, dv, dg, dbias); batched
     when the tensors have a leading batch axis."""
     lead, n, h, d, dt, dev = _common(q, k, v, g, bias, mask)
-    _check("out", out, lead + (n, n, h, d), q.dtype, dev)
-    _check("dout", dout, lead + (n, n, h, d), q.dtype, dev)
+    _check("out", out, q.shape, q.dtype, dev)
+    _check("dout", dout, q.shape, q.dtype, dev)
     _check("lse", lse, lead + (n, n, h), torch.float32, dev)
     scale = default_scale(d) if scale is None else float(scale)
-    dq, dk, dv, dg = (torch.empty_like(q) for _ in range(4))
+    dq, dk, dv, dg = [torch.empty_like(q) for _ in range(4)]
     dbias = torch.empty_like(bias)
     one = tri_attn_bwd_workspace_bytes(node, dt, n, h, d)
     need = _batch_workspace(tri_attn_bwd_batched_workspace_bytes(node, dt, lead[0], n, h, d),
@@ -522,7 +534,7 @@ def rows_bwd(q, k, v, g, bias, out, lse, dout, mask=None, scale: Optional[float]
     _check("dout", dout, (rows, n, h, d), q.dtype, dev)
     _check("lse", lse, (rows, n, h), torch.float32, dev)
     scale = default_scale(d) if scale is None else float(scale)
-    dq, dk, dv, dg = (torch.empty_like(q) for _ in range(4))
+    dq, dk, dv, dg = [torch.empty_like(q) for _ in range(4)]
     dbp = torch.empty((n, n, h), dtype=torch.float32, device=dev)
     need = tri_attn_rows_bwd_workspace_bytes(dt, n, rows, h, d)
     if workspace is None or workspace.numel() < need:
