@@ -313,8 +313,9 @@ hipError_t launch_lnl_fwd(const LnlArgs& a, hipStream_t s) {
 // The sums over rows are regrouped so that they all come from one pass over
 // dO2 and x:  G = xhat^T dO2 [K][N] and s = sum_m dO2 [N] give
 //   dW = o1^T dO2 = gamma G + beta s^T,  dgamma = sum_n W G,  dbeta = W s.
-// Kernels: lnl_bwd_dx (dx), lnl_bwd_g (G and s per workgroup, partial
-// slabs), lnl_reduce (the slabs summed in a fixed order), lnl_finish (dW,
+// Kernels: lnl_bwd (dx and G, s together, for the attention's widths) or, for
+// other widths, lnl_bwd_dx (dx) and lnl_bwd_g (G and s); both write G and s per
+// workgroup as partial slabs.  Then lnl_reduce (the slabs summed in a fixed order), lnl_finish (dW,
 // dgamma, dbeta).
 
 // lnl_bwd_dx: persistent workgroups of LBX_WAVES waves, W resident in LDS as
