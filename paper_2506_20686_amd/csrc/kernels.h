@@ -151,7 +151,7 @@ hipError_t launch_lnl_bwd(const LnlBwdArgs& a, hipStream_t s);
 // ---- fused transition layer (trn.hip) -----------------------------------------------
 constexpr int TRN_C = 128;         // features per row (the pair channel width)
 constexpr int TRN_FC = 32;         // hidden columns per weight chunk
-constexpr int TRN_FWD_IMG = 24576; // bytes of one chunk's forward weight image
+constexpr int TRN_FWD_IMG = 27648; // bytes of one chunk's forward weight image
 constexpr int TRN_BWD_IMG = 45056; // bytes of one chunk's backward weight image
 constexpr int TRN_GROUP = 128;     // hidden columns per workgroup of the weight-gradient kernel
 

@@ -32,6 +32,7 @@
 // contraction slots of the accumulator-fed operands already in accumulator
 // order); a workgroup streams them into an LDS ring.
 #include <algorithm>
+#include <type_traits>
 
 #include "dma.h"
 #include "kernels.h"
@@ -49,7 +50,7 @@ constexpr int TRN_NT = TRN_C / 16;  // MFMA steps over the features
 constexpr int TRN_ROWS = 32 * TRN_WAVES;  // rows per workgroup block
 
 // image layout of one chunk j (hidden columns fb = 32 j .. fb + 31), bytes:
-//   forward : A1a [0, 8K)    A1b [8K, 16K)    A2 [16K, 24K)
+//   forward : A1a [0, 8.5K)  A1b [8.5K, 17K)  A2 [17K, 27K)
 //   backward: A1a [0, 8.5K)  A1b [8.5K, 17K)  A3 [17K, 25.5K)  A4 [25.5K, 43.5K), padded to 44K
 // A1a / A1b: W1^T rows fb + r (a) / F + fb + r (b), 16 chunks of 8 features.
 // A2: W2^T for output tile t, row r = output column 32 t + r, 4 chunks
@@ -58,23 +59,18 @@ constexpr int TRN_ROWS = 32 * TRN_WAVES;  // rows per workgroup block
 // A4: W1 for feature tile t, row r = feature 32 t + r, 8 chunks (k-step
 //     s = 0..3, half g): s < 2 the a columns, s >= 2 the b columns of the
 //     chunk, in accumulator order.
-// Forward rows are bank-permuted (below).  Every backward row is followed by
-// 16 unused bytes instead: rows r, r + 1, .. then start an odd number of
-// 16-byte pieces apart, so an operand read (one piece of 32 consecutive
-// rows) is free of bank conflicts and all of a lane's reads of a chunk are
-// one address plus constants (the permutation takes 24 address registers,
-// which the dx kernel spends on operands in flight instead).
-constexpr int OFF_A1B = 8192, OFF_A2 = 16384;                     // forward
-constexpr int P1 = 256 + 16, P4 = 128 + 16;                       // backward row pitches
-constexpr int OFF_B1B = 32 * P1, OFF_A3 = 64 * P1, OFF_A4 = 96 * P1;
+// Every row is followed by 16 unused bytes: rows r, r + 1, .. then start an
+// odd number of 16-byte pieces apart, so an operand read (one piece of 32
+// consecutive rows) is free of bank conflicts and all of a lane's reads of a
+// chunk are one address per row pitch plus constants (a permutation of the
+// pieces takes 16 to 24 address registers, which the kernels spend on
+// operands in flight instead).
+constexpr int P1 = 256 + 16, P2 = 64 + 16, P4 = 128 + 16;         // row pitches
+constexpr int OFF_A1B = 32 * P1, OFF_A2 = 64 * P1;                // forward
+constexpr int OFF_A3 = 64 * P1, OFF_A4 = 96 * P1;                 // backward
+static_assert(OFF_A2 + 128 * P2 <= TRN_FWD_IMG && TRN_FWD_IMG % 1024 == 0, "image size");
 static_assert(OFF_A4 + 128 * P4 <= TRN_BWD_IMG && TRN_BWD_IMG % 1024 == 0, "image size");
 
-// 256-byte rows: chunk c of row r at slot c ^ (r % 16).
-__device__ inline uint32_t w256_off(int r, int c) { return r * 256 + 16 * (c ^ (r & 15)); }
-// A2 tile rows of 64 bytes.
-__device__ inline uint32_t a2_off(int t, int r, int c) {
-  return t * 2048 + r * 64 + 16 * (c ^ ((r >> 2) & 3));
-}
 // Accumulator order of a 16-wide contraction step s: slot e of half g holds
 // index 16 s + 8 (e / 4) + 4 g + e % 4 (the rows a 32x32 accumulator gives
 // a lane in its registers 8 s .. 8 s + 7).
@@ -98,19 +94,20 @@ __global__ __launch_bounds__(256) void trn_pack_kernel(const bf16* w1, const bf1
   const int j = (int)(idx / per), q = (int)(idx % per), o = 16 * q, fb = TRN_FC * j;
   const int n1 = 2 * f;  // W1 row length
   bf16x8 v = {};         // padding pieces stay zero
-  if (bwd ? o < OFF_A3 : q < 1024) {  // A1a, A1b
-    const int half = bwd ? o / OFF_B1B : q >> 9;
-    const int r = bwd ? o % OFF_B1B / P1 : (q & 511) >> 4;
-    const int c = bwd ? (o % OFF_B1B % P1) >> 4 : (q & 15) ^ (r & 15);
+  static_assert(OFF_A2 == OFF_A3, "A1a and A1b lie alike in both images");
+  if (o < OFF_A2) {  // A1a, A1b
+    const int half = o / OFF_A1B, r = o % OFF_A1B / P1, c = (o % OFF_A1B % P1) >> 4;
     const int col = half * f + fb + r;
     if (c < 16) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = w1[(int64_t)(8 * c + e) * n1 + col];
     }
   } else if (!bwd) {  // A2
-    const int q2 = q - 1024, t = q2 >> 7, r = (q2 & 127) >> 2, c = (q2 & 3) ^ ((r >> 2) & 3);
+    const int r = (o - OFF_A2) / P2, c = ((o - OFF_A2) % P2) >> 4;  // r: output column
+    if (r < TRN_C && c < 4) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = w2[(int64_t)(fb + acc_k(c >> 1, c & 1, e)) * TRN_C + 32 * t + r];
+      for (int e = 0; e < 8; ++e) v[e] = w2[(int64_t)(fb + acc_k(c >> 1, c & 1, e)) * TRN_C + r];
+    }
   } else if (o < OFF_A4) {  // A3
     const int r = (o - OFF_A3) / P1, c = ((o - OFF_A3) % P1) >> 4;
     if (c < 16) v = *(const bf16x8*)(w2 + (int64_t)(fb + r) * TRN_C + 8 * c);
@@ -125,21 +122,6 @@ __global__ __launch_bounds__(256) void trn_pack_kernel(const bf16* w1, const bf1
   }
   *(bf16x8*)(img + (int64_t)j * img_bytes + o) = v;
 }
-
-// Stream chunk images through a two-slot LDS ring: each thread copies
-// N 16-byte pieces.
-template <int N>
-struct Stage {
-  f32x4 v[N];
-  __device__ inline void load(const char* src, int tid) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = *(const f32x4*)(src + 16 * (tid + i * TRN_THREADS));
-  }
-  __device__ inline void store(char* dst, int tid) const {
-#pragma unroll
-    for (int i = 0; i < N; ++i) *(f32x4*)(dst + 16 * (tid + i * TRN_THREADS)) = v[i];
-  }
-};
 
 // Row statistics and o1 (bf16, the B operand over the features) of a lane's
 // row: half g holds features 16 t + 8 g .. + 7.
@@ -192,16 +174,6 @@ __device__ inline void load_row(const bf16* base, int64_t row, int64_t m, int g,
   for (int t = 0; t < TRN_NT; ++t) xr[t] = *(const bf16x8*)(p + 16 * t);
 }
 
-// h^T tile of the chunk in `img` (a or b half): rows = hidden columns,
-// lanes = rows of x.
-__device__ inline f32x16 h_tile(const char* img, const uint32_t (&a1)[TRN_NT],
-                                const bf16x8 (&of)[TRN_NT]) {
-  f32x16 acc = {};
-#pragma unroll
-  for (int t = 0; t < TRN_NT; ++t) acc = Mma<bf16>::mma(*(const bf16x8*)(img + a1[t]), of[t], acc);
-  return acc;
-}
-
 // Store a lane's 4 x 16 accumulated values (feature 32 t + 8 j + 4 g + i)
 // of its row as bf16, 8 bytes per run.
 __device__ inline void store_row(bf16* base, int64_t row, int g, const f32x16 (&acc)[4]) {
@@ -215,99 +187,176 @@ __device__ inline void store_row(bf16* base, int64_t row, int g, const f32x16 (&
                  (bf16)acc[t][4 * j + 3]};
 }
 
+// One chunk image HBM -> LDS by DMA, 1 KB pieces dealt to the waves in turn
+// (the last piece several times, so that no wave branches; real = false reads
+// no memory and fills the slot with zeros).  Written as instructions: after
+// the builtin the compiler holds the next LDS read, whatever it reads, until
+// the copy has landed, which put a chunk's whole copy latency into every
+// chunk of the kernels that read other slots meanwhile.  It does not count
+// these copies either, so chunk_wait() must stand before the slot's readers;
+// its own counted waits only get stricter by them.
+template <int IMG>
+__device__ inline void chunk_dma(const char* src, char* dst, int wave, int lane, bool real) {
+  constexpr int PIECES = IMG / 1024;
+  static_assert(IMG % 1024 == 0, "whole pieces");
+  const uint64_t b = (uint64_t)src;
+  const u32x4 r = {(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, real ? (uint32_t)IMG : 0u, 0x00020000u};
+  const uint32_t to = lds_addr(dst);
+#pragma unroll
+  for (int i = 0; i < (PIECES + TRN_WAVES - 1) / TRN_WAVES; ++i) {
+    const int at = 1024 * min(wave + TRN_WAVES * i, PIECES - 1);
+    // (one wait state between the write of m0 and its use; nothing else in
+    // these kernels uses m0)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(to + at),
+                 "v"(16 * lane), "s"(r), "s"(at)
+                 : "memory");
+  }
+}
+
+// Every copy, load and store of this wave has landed.
+__device__ inline void chunk_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // ---- forward -------------------------------------------------------------------------
 //
 // Persistent workgroups of 8 waves (one per CU); a workgroup takes blocks of
-// 256 rows (32 per wave) and, per block, streams the F / 32 chunk images,
-// two chunks per ring slot (one barrier per 64 hidden columns).
-
-constexpr int FWD_CPS = 2;  // chunk images per ring slot
-
+// 256 rows (32 per wave) and walks the F / 32 chunks, whose images arrive in a
+// ring of three by DMA, one barrier per chunk.  Per chunk a wave forms hb, the
+// next chunk's ha and the chunk's share of out^T, 8 MFMAs each: u of the chunk
+// is multiplied out under the next ha and the sigmoids of the next chunk run
+// under out^T and hb, so that no MFMA waits for the elementwise step; eight
+// operand fragments are in flight per wave, across chunks.  The next block's
+// rows are loaded ahead of this block's stores (loads and stores retire in
+// order).  Weights copied through registers and reads left to the compiler
+// measured 61.8 us at m = 345^2, F = 512 (forward call), against 59.4.  A
+// fragment per MFMA is the LDS's whole bandwidth at the MFMA's full rate.
 __global__ __launch_bounds__(TRN_THREADS, 1) void trn_fwd_kernel(TrnFwdArgs a) {
-  __shared__ __align__(16) char ring[2][FWD_CPS * TRN_FWD_IMG];
+  constexpr int SLOTS = 3;
+  __shared__ __align__(16) char ring[SLOTS * TRN_FWD_IMG];
   __shared__ __align__(16) float gb[2][TRN_C];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t nblk = (a.m + TRN_ROWS - 1) / TRN_ROWS;
   if ((int64_t)blockIdx.x >= nblk) return;  // whole workgroup, before any barrier
-  const int nst = a.f / TRN_FC / FWD_CPS;  // ring stages per block (F is a multiple of 128)
-  const int64_t nsteps = (nblk - blockIdx.x + gridDim.x - 1) / gridDim.x * nst;
-  constexpr int PER = FWD_CPS * TRN_FWD_IMG / 16 / TRN_THREADS;
-  Stage<PER> st;
-  st.load(a.img, tid);
+  const int nch = a.f / TRN_FC;             // at least 4 (F is a multiple of 128)
+  const int64_t nsteps = (nblk - blockIdx.x + gridDim.x - 1) / gridDim.x * nch;
+  int dj = 0, ds = 0;  // chunk index and slot of the next DMA
+  int64_t issued = 0;
+  auto issue = [&] {
+    chunk_dma<TRN_FWD_IMG>(a.img + (int64_t)dj * TRN_FWD_IMG, ring + ds * TRN_FWD_IMG, wave, lane,
+                           issued < nsteps);
+    dj = dj + 1 == nch ? 0 : dj + 1;
+    ds = ds + 1 == SLOTS ? 0 : ds + 1;
+    ++issued;
+  };
+  issue();
+  issue();
+  int64_t row = (int64_t)blockIdx.x * TRN_ROWS + wave * 32 + l32;
+  bf16x8 xr[TRN_NT], of[TRN_NT];
+  load_row(a.x, row, a.m, g, xr);
   if (tid < TRN_C) {
     gb[0][tid] = (float)a.gamma[tid];
     gb[1][tid] = (float)a.beta[tid];
   }
-  st.store(ring[0], tid);
+  chunk_wait();
   __syncthreads();
 
-  uint32_t a1[TRN_NT], a2[4][2];
+  const uint32_t base = lds_addr(ring);
+  const uint32_t b1 = base + l32 * P1 + 16 * g, b2 = base + OFF_A2 + l32 * P2 + 16 * g;
+  uint32_t so = 0;  // slot offset of the current chunk
+  bf16x8 fq[8];     // operand fragments in flight
+  auto f1a = [&](uint32_t o, int i) { return lds_load16<bf16x8>(b1 + o + 32 * i); };
+  auto f1b = [&](uint32_t o, int i) { return lds_load16<bf16x8>(b1 + o + OFF_A1B + 32 * i); };
+  // (tile i % 4, step i / 4)
+  auto f2 = [&](uint32_t o, int i) {
+    return lds_load16<bf16x8>(b2 + o + (i & 3) * 32 * P2 + 32 * (i >> 2));
+  };
 #pragma unroll
-  for (int t = 0; t < TRN_NT; ++t) a1[t] = w256_off(l32, 2 * t + g);
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int s = 0; s < 2; ++s) a2[t][s] = OFF_A2 + a2_off(t, l32, 2 * s + g);
+  for (int i = 0; i < 8; ++i) fq[i] = f1a(0, i);
 
-  int64_t step = 0;
   for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-    const int64_t row = blk * TRN_ROWS + wave * 32 + l32;
-    bf16x8 xr[TRN_NT], of[TRN_NT];
-    load_row(a.x, row, a.m, g, xr);
     float mean, rstd;
     ln_row(xr, gb, g, a.eps, mean, rstd, of);
     if (row < a.m && g == 0) {
       a.mean[row] = mean;
       a.rstd[row] = rstd;
     }
-    f32x16 acc[4] = {};
-    for (int j = 0; j < nst; ++j, ++step) {
-      const char* slot = ring[step & 1];
-      const bool more = step + 1 < nsteps;
-      if (more)
-        st.load(a.img + (int64_t)(j + 1 == nst ? 0 : j + 1) * FWD_CPS * TRN_FWD_IMG, tid);
+    f32x16 acc[4] = {}, ha = {};
+    float si[16];  // exp2, then the sigmoid, then a sigmoid(a)
+    // stage w of the gate: a pair of elements starts per stage, w = 1 .. 8
+    auto gate = [&](int w) {
 #pragma unroll
-      for (int c = 0; c < FWD_CPS; ++c) {
-        const char* cur = slot + c * TRN_FWD_IMG;
-        const f32x16 ha = h_tile(cur, a1, of);
-        const f32x16 hb = h_tile(cur + OFF_A1B, a1, of);
-        bf16x8 uf[2];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float x = ha[v];
-          uf[v >> 3][v & 7] = (bf16)(x * sigm(x) * hb[v]);
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-          for (int s = 0; s < 2; ++s)
-            acc[t] = Mma<bf16>::mma(*(const bf16x8*)(cur + a2[t][s]), uf[s], acc[t]);
+      for (int k = 0; k < 2; ++k) {
+        const int e0 = 2 * (w - 1) + k, e1 = e0 - 2, e2 = e0 - 4;
+        if (e0 >= 0 && e0 < 16) si[e0] = __builtin_amdgcn_exp2f(-LOG2E * ha[e0]);
+        if (e1 >= 0 && e1 < 16) si[e1] = __builtin_amdgcn_rcpf(1.f + si[e1]);
+        if (e2 >= 0 && e2 < 16) si[e2] = ha[e2] * si[e2];
       }
-      if (more) st.store(ring[(step + 1) & 1], tid);
-      __syncthreads();
+    };
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      ha = Mma<bf16>::mma(fq[i], of[i], ha);
+      fq[i] = f1b(so, i);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (row < a.m) store_row(a.out, row, g, acc);
+#pragma unroll
+    for (int w = 0; w < 8; ++w) gate(w);
+    auto chunk = [&](auto lastc) {
+      constexpr bool LAST = decltype(lastc)::value;  // the block's last chunk: no next ha
+      chunk_wait();  // the next chunk has landed; every wave has left the previous one
+      lds_barrier();
+      issue();
+      const uint32_t sn = so == (SLOTS - 1) * TRN_FWD_IMG ? 0u : so + TRN_FWD_IMG;
+      f32x16 hb = {};
+      bf16x8 uf[2];
+      auto mul = [&](int w) {  // u of elements 2 w, 2 w + 1
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const int e = 2 * w + k;
+          if (e >= 0) uf[e >> 3][e & 7] = (bf16)(si[e] * hb[e]);
+        }
+      };
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        hb = Mma<bf16>::mma(fq[i], of[i], hb);
+        fq[i] = LAST ? f2(so, i) : f1a(sn, i);
+        gate(8 + i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (LAST) {
+#pragma unroll
+        for (int w = 0; w < 8; ++w) mul(w);
+      } else {
+        ha = f32x16{};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          ha = Mma<bf16>::mma(fq[i], of[i], ha);
+          fq[i] = f2(so, i);
+          mul(i - 1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        mul(7);
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        acc[i & 3] = Mma<bf16>::mma(fq[i], uf[i >> 2], acc[i & 3]);
+        fq[i] = LAST ? f1a(sn, i) : f1b(sn, i);
+        if constexpr (!LAST) gate(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      so = sn;
+    };
+    for (int j = 0; j + 1 < nch; ++j) chunk(std::false_type{});
+    chunk(std::true_type{});
+    const int64_t done = row;
+    row += (int64_t)gridDim.x * TRN_ROWS;
+    load_row(a.x, row, a.m, g, xr);  // (past the last block: the last row again)
+    __builtin_amdgcn_sched_barrier(0);
+    if (done < a.m) store_row(a.out, done, g, acc);
   }
+  chunk_wait();  // the copies past the last chunk land before the workgroup ends
 }
 
 // ---- backward: dx ----------------------------------------------------------------------
-
-// One chunk image HBM -> LDS by DMA, 1 KB pieces dealt to the waves in turn
-// (the last piece several times, so that no wave branches; real = false reads
-// no memory and fills the slot with zeros).
-template <int IMG>
-__device__ inline void chunk_dma(const char* src, char* dst, int wave, int lane, bool real) {
-  constexpr int PIECES = IMG / 1024;
-  static_assert(IMG % 1024 == 0, "whole pieces");
-  const rsrc_t r = buf_rsrc_n(src, real ? (uint32_t)IMG : 0u);
-#pragma unroll
-  for (int i = 0; i < (PIECES + TRN_WAVES - 1) / TRN_WAVES; ++i) {
-    const int piece = min(wave + TRN_WAVES * i, PIECES - 1);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (TRIATTN_LDS void*)(dst + 1024 * piece), 16,
-                                             16 * lane, 1024 * piece, 0, 0);
-  }
-}
 
 // Persistent workgroups of 8 waves as in the forward, 32 rows per wave.  Per
 // chunk a wave forms du, ha and hb (24 MFMAs) and adds the chunk's share of
@@ -349,7 +398,7 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_dx_kernel(TrnBwdArgs a
     gb[0][tid] = (float)a.gamma[tid];
     gb[1][tid] = (float)a.beta[tid];
   }
-  wait_vm<0>();
+  chunk_wait();
   __syncthreads();
 
   const uint32_t base = lds_addr(ring);
@@ -361,7 +410,7 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_dx_kernel(TrnBwdArgs a
   bf16x8 fq[NQ];
   auto frag = [&](uint32_t o, int i) {
     if (i < 24) {
-      const int off = i < 8 ? OFF_A3 : (i < 16 ? 0 : OFF_B1B);
+      const int off = i < 8 ? OFF_A3 : (i < 16 ? 0 : OFF_A1B);
       return lds_load16<bf16x8>(b1 + o + off + 32 * (i & 7));
     }
     const int s = ((i - 24) >> 2) ^ 2, t = i & 3;
@@ -422,7 +471,7 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_dx_kernel(TrnBwdArgs a
         valu(i);
         __builtin_amdgcn_sched_barrier(0);
       }
-      wait_vm<0>();  // the next chunk has landed; every wave has left the previous one
+      chunk_wait();  // the next chunk has landed; every wave has left the previous one
       lds_barrier();
       issue();
 #pragma unroll
@@ -461,7 +510,7 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_dx_kernel(TrnBwdArgs a
       for (int v = 0; v < 16; ++v) dx[t][v] = (wdy[t][v] - c1 * xh[t][v] - c2) * rstd;
     if (row < a.m) store_row(a.dx, row, g, dx);
   }
-  wait_vm<0>();  // the copies past the last chunk land before the workgroup ends
+  chunk_wait();  // the copies past the last chunk land before the workgroup ends
 }
 
 // ---- backward: sums over rows ----------------------------------------------------------
@@ -539,7 +588,7 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_w_kernel(TrnBwdArgs a,
   for (int s = 0; s < 4; ++s) {
     const char* o = img + ((f0 & 31) + l16) * P1 + 16 * (4 * s + q);
     w1a[s] = *(const bf16x8*)o;
-    w1b[s] = *(const bf16x8*)(o + OFF_B1B);
+    w1b[s] = *(const bf16x8*)(o + OFF_A1B);
     w2r[s] = *(const bf16x8*)(o + OFF_A3);
   }
 
