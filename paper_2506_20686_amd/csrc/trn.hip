@@ -229,6 +229,8 @@ __device__ inline void chunk_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "mem
 // order).  Weights copied through registers and reads left to the compiler
 // measured 61.8 us at m = 345^2, F = 512 (forward call), against 59.4.  A
 // fragment per MFMA is the LDS's whole bandwidth at the MFMA's full rate.
+// 64 rows per wave halve that, but at one wave per SIMD the same schedule
+// (442 registers) took 71.6 us.
 __global__ __launch_bounds__(TRN_THREADS, 1) void trn_fwd_kernel(TrnFwdArgs a) {
   constexpr int SLOTS = 3;
   __shared__ __align__(16) char ring[SLOTS * TRN_FWD_IMG];
