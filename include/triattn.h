@@ -49,7 +49,8 @@
  *     work is enqueued on `stream` (a hipStream_t; NULL is the default stream)
  *     and the caller supplies a device workspace of at least the size the
  *     matching *_workspace_bytes call reports.  Outputs are fully
- *     overwritten.  Calls that share a workspace must not overlap.
+ *     overwritten (and may hold intermediate values until the call's work
+ *     ends).  Calls that share a workspace must not overlap.
  *   - Errors: every function returns a triattn_status.  Arguments are checked
  *     before any HIP call is made, so an invalid call has no effect.  A HIP
  *     launch failure returns TRIATTN_ERR_HIP.  Nothing aborts.

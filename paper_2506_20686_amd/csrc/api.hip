@@ -42,30 +42,23 @@ bool padded16(int64_t d, int dtype) { return d == 16 && dtype != TRIATTN_BF16; }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-// Row chunks of the bias-gradient reduction over nr rows (partial slabs).
-// Each workgroup of the bias-gradient kernel takes 128 queries x 128 keys of
-// one head over one chunk of rows and fills a CU on its own, so the kernel
-// runs in rounds of 256 workgroups.  The cost model, in units of one row's
-// work: per round the chunk's rows plus about 3.3 for the workgroup's fixed
-// work (bias tile, pipeline fill, slab store), plus, per slab, the reduction
-// that reads it back.  A slab costs about 1 where it is large (N = 768, four
-// heads: 9.4 MB); where sixteen chunks would leave half of the chip idle
-// (tiles <= 8, up to 128 tokens at four heads) its 16 .. 260 KB cost little
-// more than a tenth, and up to 32 chunks are taken.  Measured (events around
-// the launch, 5 us included), before -> after: fp32 N = 32, 4 -> 16 chunks, dB
-// 22.1 -> 10.0 us, its reduction 8.1 -> 8.9; bf16 N = 100, 10 -> 25 chunks,
-// 20.6 -> 15.0 and 16 -> 11.3.
+// Row chunks of the bias-gradient reduction over nr rows (partial slabs) that
+// the workspace has room for, at most 16.  Each workgroup of the
+// bias-gradient kernel takes 128 queries x 128 keys of one head over one chunk
+// of rows and fills a CU on its own, so the kernel runs in rounds of 256
+// workgroups.  The cost model, in units of one row's work: per round the
+// chunk's rows plus about 3.3 for the workgroup's fixed work (bias tile,
+// pipeline fill, slab store), plus about 1 per slab for the reduction that
+// reads the slabs back.
+int64_t db_tiles(int64_t n, int64_t h) { return h * ((n + 127) / 128) * ((n + 127) / 128); }
 int db_row_chunks(int64_t n, int64_t nr, int64_t h) {
-  const int64_t tiles = h * ((n + 127) / 128) * ((n + 127) / 128);
-  const bool small = tiles <= 8;
-  const double np = (double)((n + 31) / 32 * 32);
-  const double slab = small ? 0.1 + (double)h * np * np / (4.0 * 768 * 768) : 1.0;
+  const int64_t tiles = db_tiles(n, h);
   int best = 1;
   double best_cost = 1e300;
-  for (int64_t c = 1; c <= (small ? 32 : 16) && c <= nr; ++c) {
+  for (int64_t c = 1; c <= 16 && c <= nr; ++c) {
     const int64_t rpc = (nr + c - 1) / c, chunks = (nr + rpc - 1) / rpc;
     const int64_t rounds = (tiles * chunks + 255) / 256;
-    const double cost = (double)rounds * ((double)rpc + 3.3) + slab * (double)chunks;
+    const double cost = (double)rounds * ((double)rpc + 3.3) + (double)chunks;
     if (cost < best_cost) {
       best_cost = cost;
       best = (int)chunks;
@@ -74,9 +67,33 @@ int db_row_chunks(int64_t n, int64_t nr, int64_t h) {
   return best;
 }
 
+// Row chunks of a small map, `spare` slabs of which fit outside the workspace
+// (in dK's place, see launch_bwd).  The model above charges a slab of 16 ..
+// 260 KB what one of 9 MB costs (N = 768); with up to four tiles (128 tokens at
+// four heads) a chip is nearly empty, and up to 16 chunks of at least four
+// rows are taken.  The count serves a batch too (its samples give the same
+// bits as unbatched ones), which fills the chip by itself and pays each
+// chunk's fixed work: hence the line at four tiles and 16 chunks, where four
+// maps still run in one round.  dB + reduction, events around both launches
+// (10 us included), N x heads, chunks by the model -> here; one map, 16 maps:
+//   fp32 32 x 4   4 ->  8   28 -> 21 us    29 ->  32 us
+//   fp32 64 x 4   8 -> 16   38 -> 27       68 ->  75
+//   fp32 128 x 4 10 -> 16   81 -> 58      244 -> 225
+//   bf16 64 x 4   8 -> 16   21 -> 20       41 ->  49
+//   bf16 128 x 4 10 -> 16   30 -> 28      129 -> 145
+// More chunks gain one map little more and cost 16 maps much (bf16 128 x 4, 32
+// chunks: 28 and 184 us); with eight tiles three maps already lose (fp32
+// 160 x 2, 10 -> 16: 95 -> 69 us for one map, 97 -> 124 for three).
+int db_small_chunks(int64_t n, int64_t nr, int64_t h, int chunks, int64_t spare) {
+  if (db_tiles(n, h) > 4) return chunks;
+  const int64_t most = std::min<int64_t>(16, chunks + spare);
+  const int64_t rpc = std::max<int64_t>(4, (nr + most - 1) / most);
+  return std::max(chunks, (int)((nr + rpc - 1) / rpc));
+}
+
 struct Layout {
   size_t bt, btT, kbits, rowfull, lse2, dsum, da, dalo, slabs, total;
-  int nrc;
+  int nrc, nws;
 };
 
 // Workspace layout for nr rows of pair length n (offsets in bytes, each
@@ -84,7 +101,7 @@ struct Layout {
 //   forward : bt [H][np][np] f32, kbits [nr][np/32] u32, rowfull [nr] u32
 //   backward: bt, btT [H][np][np] f32, kbits, rowfull, lse2 and dsum [H][nr][np] f32,
 //             dA [nr][n][H][32] dtype (bf16: plus its low part, same size),
-//             slabs [nrc][H][np][np] f32
+//             slabs [nws][H][np][np] f32 (the other nrc - nws lie in dK's place)
 Layout plan(bool bwd, int dtype, int64_t n, int64_t nr, int64_t h, int64_t kd = 32) {
   const size_t np = (size_t)((n + 31) / 32 * 32);
   const size_t plane = (size_t)h * np * np * sizeof(float);
@@ -111,9 +128,10 @@ Layout plan(bool bwd, int dtype, int64_t n, int64_t nr, int64_t h, int64_t kd = 
     off += round256(pair);
     L.dalo = off;
     if (dtype == TRIATTN_BF16) off += round256(pair);
-    L.nrc = db_row_chunks(n, nr, h);
+    L.nws = db_row_chunks(n, nr, h);
+    L.nrc = db_small_chunks(n, nr, h, L.nws, (int64_t)(pair / plane));
     L.slabs = off;
-    off += round256((size_t)L.nrc * plane);
+    off += round256((size_t)L.nws * plane);
   }
   L.total = off;
   return L;
@@ -168,7 +186,7 @@ int run_bwd(int node, const Geom& g, const Layout& L, const void* q, const void*
   char* b = (char*)ws;
   const triattn::BwdWs w{(float*)(b + L.lse2), (float*)(b + L.dsum), (void*)(b + L.da),
                          std::is_same<T, float>::value ? nullptr : (void*)(b + L.dalo),
-                         (float*)(b + L.slabs), L.nrc};
+                         (float*)(b + L.slabs), L.nrc, L.nws};
   if (triattn::launch_bwd<T>(g, node, p, w, (const T*)bias, mask, (const T*)q, (const T*)k, (const T*)v,
                              (const T*)gate, (const T*)out, lse, (const T*)dout, (T*)dq, (T*)dk,
                              (T*)dv, (T*)dg, (T*)dbias, dbias_f32, s) != hipSuccess)

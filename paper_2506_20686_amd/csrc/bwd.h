@@ -29,6 +29,7 @@ struct BwdArgs {
   float* slabs;
   int nblk;  // 128-wide blocks per axis
   int nrc;   // row chunks (db)
+  int nws;   // slabs held in `slabs`; the others lie in dK's place
   int rpc;   // rows per chunk (db)
 };
 
@@ -52,6 +53,20 @@ __device__ inline void to_sample(BwdArgs<T>& a) {
   a.dq = at_sample(a.dq, G.bPair);
   a.dk = at_sample(a.dk, G.bPair);
   a.dv = at_sample(a.dv, G.bPair);
+}
+
+// The map [np][np] of head h in the slab of row chunk rc.  Worked out at a
+// kernel's start and held (two scalar registers, opaque to the compiler, which
+// would otherwise keep everything it is made of).
+template <typename T>
+__device__ inline float* db_slab(const BwdArgs<T>& a, int rc, int h) {
+  const Geom& G = a.g;
+  const int64_t plane = (int64_t)G.np * G.np;
+  const bool spare = rc >= a.nws;
+  uint64_t p = (uint64_t)((spare ? (float*)a.dk : a.slabs) +
+                          ((int64_t)(spare ? rc - a.nws : rc) * G.H + h) * plane);
+  asm volatile("" : "+s"(p));
+  return (float*)p;
 }
 
 // dK and dV (dkdv.hip): the DMA kernels for bf16 (16, 32 or 64 channels), the

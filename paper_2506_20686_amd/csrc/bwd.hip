@@ -678,6 +678,7 @@ __global__ __launch_bounds__(512, 1) void db_kernel(BwdArgs<T> a) {
   const int qb = (w / a.nblk) % a.nblk;
   const int rc = (w / (a.nblk * a.nblk)) % a.nrc;
   const int h = w / (a.nblk * a.nblk * a.nrc);
+  float* const map = db_slab(a, rc, h);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
   const int qw = (wave & 3) * TILE;  // this wave's queries within the block
   const int q0 = qb * DB_ROWS + qw;
@@ -783,7 +784,7 @@ __global__ __launch_bounds__(512, 1) void db_kernel(BwdArgs<T> a) {
     __syncthreads();
   }
   if (!active) return;
-  float* slab = a.slabs + (((int64_t)rc * G.H + h) * G.np + q0 + l32) * G.np + 4 * g;
+  float* slab = map + (int64_t)(q0 + l32) * G.np + 4 * g;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const int kt = kt0 + 2 * kh + u;
@@ -833,6 +834,7 @@ __global__ __launch_bounds__(1024) void db_dma_kernel(BwdArgs<bf16> a, int nkb) 
   const int qb = (w / nkb) % nqb;
   const int rc = (w / (nkb * nqb)) % a.nrc;
   const int h = w / (nkb * nqb * a.nrc);
+  float* const map = db_slab(a, rc, h);
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qtl = wave & 3, ktl = wave >> 2;
@@ -1024,8 +1026,7 @@ __global__ __launch_bounds__(1024) void db_dma_kernel(BwdArgs<bf16> a, int nkb) 
     run(std::false_type{});
   wait_vm<0>();  // the copies past the end must land before the workgroup ends
   if (!active) return;
-  float* slab = a.slabs + (((int64_t)rc * G.H + h) * G.np + qstart + qtl * TILE + l32) * G.np +
-                kt * TILE + 4 * g;
+  float* slab = map + (int64_t)(qstart + qtl * TILE + l32) * G.np + kt * TILE + 4 * g;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     f32x4 x;
@@ -1064,6 +1065,7 @@ __global__ __launch_bounds__(64 * D6_WAVES) void db_dma64_kernel(BwdArgs<bf16> a
   const int qb = (w / nkb) % nqb;
   const int rc = (w / (nkb * nqb)) % a.nrc;
   const int h = w / (nkb * nqb * a.nrc);
+  float* const map = db_slab(a, rc, h);
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qtl = wave & 1, ktl = wave >> 1;
@@ -1222,8 +1224,7 @@ __global__ __launch_bounds__(64 * D6_WAVES) void db_dma64_kernel(BwdArgs<bf16> a
   }
   wait_vm<0>();  // the copies past the end must land before the workgroup ends
   if (!active) return;
-  float* slab = a.slabs + (((int64_t)rc * G.H + h) * G.np + qstart + qtl * TILE + l32) * G.np +
-                kt * TILE + 4 * g;
+  float* slab = map + (int64_t)(qstart + qtl * TILE + l32) * G.np + kt * TILE + 4 * g;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     f32x4 x;
@@ -1246,9 +1247,11 @@ __global__ __launch_bounds__(64 * D6_WAVES) void db_dma64_kernel(BwdArgs<bf16> a
 // N = 201: 20 and 11).
 constexpr int DBR_HG = 4;  // heads per pass
 template <typename T>
-__global__ __launch_bounds__(256) void db_reduce_kernel(Geom G, int node, int nrc,
-                                                        const float* slabs, T* dbias) {
+__global__ __launch_bounds__(256) void db_reduce_kernel(Geom G, int node, int nrc, int nws,
+                                                        const float* slabs, const float* spare,
+                                                        int64_t bSpare, T* dbias) {
   slabs = ws_at_sample(slabs, G.bWs);
+  spare = ws_at_sample(spare, bSpare);  // the slabs past the first nws
   dbias = at_sample(dbias, G.bBias);
   const int nt = G.nkt, n = G.n, tid = threadIdx.x;
   const int qa = blockIdx.x % nt, kb = blockIdx.x / nt;
@@ -1258,16 +1261,22 @@ __global__ __launch_bounds__(256) void db_reduce_kernel(Geom G, int node, int nr
   for (int h0 = 0; h0 < G.H; h0 += DBR_HG) {
     const int hn = min(DBR_HG, G.H - h0);
     if (h0 > 0) __syncthreads();  // the previous pass's stores have read the tile
-    const float* p = slabs + (int64_t)h0 * plane + (int64_t)(32 * qa + r) * G.np + 32 * kb + c0;
+    const int64_t at = (int64_t)h0 * plane + (int64_t)(32 * qa + r) * G.np + 32 * kb + c0;
+    const int64_t size = G.H * plane;  // of a slab
+    const float* p = slabs + at;
+    const float* ps = spare + at - nws * size;  // slab c >= nws, as p for the others
     if (hn == DBR_HG) {  // the heads' sums side by side: 4 x 4 reads in flight
       f32x4 sum[DBR_HG];
 #pragma unroll
       for (int hh = 0; hh < DBR_HG; ++hh) sum[hh] = *(const f32x4*)(p + hh * plane);
+      auto add = [&](const float* s, int from, int to) {
 #pragma unroll 4
-      for (int c = 1; c < nrc; ++c)
+        for (int c = from; c < to; ++c)
 #pragma unroll
-        for (int hh = 0; hh < DBR_HG; ++hh)
-          sum[hh] += *(const f32x4*)(p + ((int64_t)c * G.H + hh) * plane);
+          for (int hh = 0; hh < DBR_HG; ++hh) sum[hh] += *(const f32x4*)(s + c * size + hh * plane);
+      };
+      add(p, 1, nws);
+      add(ps, nws, nrc);
 #pragma unroll
       for (int hh = 0; hh < DBR_HG; ++hh)
 #pragma unroll
@@ -1275,8 +1284,12 @@ __global__ __launch_bounds__(256) void db_reduce_kernel(Geom G, int node, int nr
     } else {
       for (int hh = 0; hh < hn; ++hh) {
         f32x4 sum = *(const f32x4*)(p + hh * plane);
+        auto add = [&](const float* s, int from, int to) {
 #pragma unroll 8
-        for (int c = 1; c < nrc; ++c) sum += *(const f32x4*)(p + ((int64_t)c * G.H + hh) * plane);
+          for (int c = from; c < to; ++c) sum += *(const f32x4*)(s + c * size + hh * plane);
+        };
+        add(p, 1, nws);
+        add(ps, nws, nrc);
 #pragma unroll
         for (int e = 0; e < 4; ++e) tl[hh][r][c0 + e] = sum[e];
       }
@@ -1334,7 +1347,7 @@ hipError_t launch_bwd(const Geom& g, int node, const Prep& p, const BwdWs& ws, c
     }
   }
   BwdArgs<T> a{g, p.bt, p.btT, p.kbits, p.rowfull, q, k, v, da, dalo, ws.lse2, ws.dsum, dq, dk, dv, ws.slabs,
-               (g.n + BWD_BLK - 1) / BWD_BLK, ws.nrc, (g.nr + ws.nrc - 1) / ws.nrc};
+               (g.n + BWD_BLK - 1) / BWD_BLK, ws.nrc, ws.nws, (g.nr + ws.nrc - 1) / ws.nrc};
   const int64_t nrow = (int64_t)a.nblk * g.nr * g.H;
   {
     // the dQ kernel first: it produces D for the other two
@@ -1354,9 +1367,17 @@ hipError_t launch_bwd(const Geom& g, int node, const Prep& p, const BwdWs& ws, c
       hipLaunchKernelGGL((dq_kernel<T, 32>), dim3((unsigned)nrow, 1, (unsigned)g.batch), dim3(256), 0, s, a);
     }
   }
-  {
+  // Slabs that the workspace has no room for lie in dK's place: dK is computed
+  // last then.  (The outputs' contents are this call's until it ends; dV and
+  // the others are not used so, which lets a caller that drops some gradients
+  // pass one buffer for them.)
+  const bool spare = ws.nrc > ws.nws;
+  auto dkdv = [&] {
     KernelTimer t(K_DKDV, s);
-    const hipError_t e = launch_dkdv(a, node, s);
+    return launch_dkdv(a, node, s);
+  };
+  if (!spare) {
+    const hipError_t e = dkdv();
     if (e != hipSuccess) return e;
   }
   {
@@ -1384,12 +1405,17 @@ hipError_t launch_bwd(const Geom& g, int node, const Prep& p, const BwdWs& ws, c
   {
     const unsigned nblk = (unsigned)(g.nkt * g.nkt);
     KernelTimer t(K_DB_REDUCE, s);
+    const int64_t bdk = g.bPair * (int64_t)sizeof(T);  // bytes between the samples' dK
     if (dbias_f32)
       hipLaunchKernelGGL(db_reduce_kernel<float>, dim3(nblk, 1, (unsigned)g.batch), dim3(256), 0, s, g, node,
-                         ws.nrc, ws.slabs, dbias_f32);
+                         ws.nrc, ws.nws, ws.slabs, (const float*)dk, bdk, dbias_f32);
     else
       hipLaunchKernelGGL(db_reduce_kernel<T>, dim3(nblk, 1, (unsigned)g.batch), dim3(256), 0, s, g, node, ws.nrc,
-                         ws.slabs, dbias);
+                         ws.nws, ws.slabs, (const float*)dk, bdk, dbias);
+  }
+  if (spare) {
+    const hipError_t e = dkdv();
+    if (e != hipSuccess) return e;
   }
   return hipGetLastError();
 }

@@ -62,8 +62,9 @@ struct BwdWs {
   float* dsum;   // [H][nr][np]  -D, D = rowsum(dO * O) (stored negated: it enters as -D)
   void* da;      // [nr][n][H][32] dtype: dA = dO * sigmoid(G), laid out like dO
   void* dalo;    // bf16 only: dA - bf16(dA) rounded to bf16 (null for fp32)
-  float* slabs;  // [nrc][H][np][np] per-row-chunk partial bias gradients
+  float* slabs;  // [nws][H][np][np] per-row-chunk partial bias gradients
   int nrc;       // row chunks of the bias-gradient reduction
+  int nws;       // slabs in the workspace; the other nrc - nws lie in dK's place
 };
 
 template <typename T>

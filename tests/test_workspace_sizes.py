@@ -1,0 +1,33 @@
+"""Workspace sizes (CPU).  A call takes a workspace of the size that the
+matching query reports and refuses a smaller one, so callers that hold a
+buffer of a size once reported are served only while it does not grow: no
+query may report more than it did (the figures here)."""
+import pytest
+
+from paper_2506_20686_amd import binding as B
+
+ATTN_BWD = {  # (dtype, n, h, d): bytes
+    (B.F32, 24, 4, 32): 418304, (B.F32, 32, 4, 32): 655872, (B.F32, 32, 4, 16): 5898752,
+    (B.F32, 64, 4, 32): 2884352, (B.F32, 100, 4, 16): 59877632, (B.F32, 100, 4, 64): 13797632,
+    (B.F32, 128, 4, 32): 12061184, (B.F32, 256, 2, 32): 27272192,
+    (B.BF16, 2, 4, 32): 53760, (B.BF16, 16, 2, 32): 123392, (B.BF16, 24, 4, 32): 418304,
+    (B.BF16, 32, 4, 32): 655872, (B.BF16, 32, 4, 16): 393728, (B.BF16, 64, 4, 32): 2884352,
+    (B.BF16, 100, 4, 32): 8677632, (B.BF16, 100, 4, 16): 6117632,
+    (B.BF16, 128, 4, 32): 12061184, (B.BF16, 128, 8, 32): 24119808,
+    (B.BF16, 129, 2, 32): 7051776, (B.BF16, 256, 1, 32): 13640704,
+    (B.BF16, 256, 2, 32): 27272192, (B.BF16, 768, 4, 32): 405875712,
+}
+
+
+@pytest.mark.parametrize("key", ATTN_BWD)
+def test_attention_backward(key):
+    dtype, n, h, d = key
+    for node in (B.STARTING, B.ENDING):
+        assert B.tri_attn_bwd_workspace_bytes(node, dtype, n, h, d) <= ATTN_BWD[key]
+
+
+def test_batched_and_row_ranges():
+    assert B.tri_attn_bwd_batched_workspace_bytes(0, B.BF16, 3, 100, 4, 32) <= 26032896
+    for n, rows, size in ((32, 7, 187904), (100, 30, 3494656), (128, 16, 2687488),
+                          (128, 1, 856576)):
+        assert B.tri_attn_rows_bwd_workspace_bytes(B.BF16, n, rows, 4, 32) <= size
