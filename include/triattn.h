@@ -301,8 +301,8 @@ int tri_attn_timing_enable(int on);
  * needs.  Process-wide, like tri_attn_timing_enable.  Returns TRIATTN_OK. */
 int tri_attn_timing_select(uint64_t mask);
 
-/* Waits for the recorded events of kernel `index` (0, 1, ... in launch-site
- * order; TRIATTN_ERR_INVALID_ARG past the last one) and returns its name
+/* Waits for the recorded events of kernel `index` (0, 1, ..., fixed numbers;
+ * TRIATTN_ERR_INVALID_ARG past the last one) and returns its name
  * (static string), the summed elapsed milliseconds and the launch count
  * since the last reset.  TRIATTN_ERR_HIP if an event call failed. */
 int tri_attn_timing_read(int index, const char** name, double* total_ms, int64_t* launches);

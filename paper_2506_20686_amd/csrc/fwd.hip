@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256) void prep_kernel(Geom G, int node, int nkb, co
 template <typename T>
 hipError_t launch_prep(const Geom& g, int node, const T* bias, const uint8_t* mask, const Prep& p,
                        hipStream_t s) {
-  KernelTimer t(K_PREP, s);
+  KernelTimer t(K_PREP_BIAS, s);
   hipLaunchKernelGGL(prep_kernel<T>, dim3(prep_blocks(g, node), 1, (unsigned)g.batch), dim3(256), 0,
                      s, g, node, (int)prep_kbits_blocks(g, node), bias, mask, p);
   return hipGetLastError();

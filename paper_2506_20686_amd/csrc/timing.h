@@ -6,10 +6,16 @@
 
 namespace triattn {
 
+// The numbers are the indices (and mask bits) that callers hold, so a kernel
+// that goes leaves its number unused: the forward's preparation, one launch,
+// counts as K_PREP_BIAS, the backward's as K_BWD_PREP; K_PREP_KBITS and
+// K_BWD_PAD count nothing.
 enum KernelId {
-  K_PREP,
+  K_PREP_BIAS,
+  K_PREP_KBITS,
   K_FWD,
   K_BWD_PREP,
+  K_BWD_PAD,
   K_DQ,
   K_DKDV,
   K_DB,
