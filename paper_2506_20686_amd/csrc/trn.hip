@@ -201,16 +201,37 @@ __device__ inline void chunk_dma(const char* src, char* dst, int wave, int lane,
   static_assert(IMG % 1024 == 0, "whole pieces");
   const uint64_t b = (uint64_t)src;
   const u32x4 r = {(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, real ? (uint32_t)IMG : 0u, 0x00020000u};
-  const uint32_t to = lds_addr(dst);
+  const uint32_t to = lds_addr(dst), v = 16 * lane;
+  constexpr int N = (PIECES + TRN_WAVES - 1) / TRN_WAVES;
+  static_assert(N == 4 || N == 6, "pieces per wave");
+  uint32_t at[N], m[N];
 #pragma unroll
-  for (int i = 0; i < (PIECES + TRN_WAVES - 1) / TRN_WAVES; ++i) {
-    const int at = 1024 * min(wave + TRN_WAVES * i, PIECES - 1);
-    // (one wait state between the write of m0 and its use; nothing else in
-    // these kernels uses m0)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(to + at),
-                 "v"(16 * lane), "s"(r), "s"(at)
-                 : "memory");
+  for (int i = 0; i < N; ++i) {
+    at[i] = 1024 * min(wave + TRN_WAVES * i, PIECES - 1);
+    m[i] = to + at[i];
   }
+  // m0 (the LDS address) is an operand, so that the compiler knows what it
+  // holds.  It does not see to the wait states here: five before the first
+  // load, in case a scalar operand has just come back from a vector register,
+  // and one after a write of m0.
+#define TRN_COPY(m, s) "s_mov_b32 m0, " m "\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, " s " offen lds\n\t"
+  uint32_t m0 = m[0];
+  if constexpr (N == 4)
+    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
+                 TRN_COPY("%4", "%5") TRN_COPY("%6", "%7") TRN_COPY("%8", "%9")
+                 : "+{m0}"(m0)
+                 : "v"(v), "s"(r), "s"(at[0]), "s"(m[1]), "s"(at[1]), "s"(m[2]), "s"(at[2]),
+                   "s"(m[3]), "s"(at[3])
+                 : "memory");
+  else
+    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
+                 TRN_COPY("%4", "%5") TRN_COPY("%6", "%7") TRN_COPY("%8", "%9")
+                 TRN_COPY("%10", "%11") TRN_COPY("%12", "%13")
+                 : "+{m0}"(m0)
+                 : "v"(v), "s"(r), "s"(at[0]), "s"(m[1]), "s"(at[1]), "s"(m[2]), "s"(at[2]),
+                   "s"(m[3]), "s"(at[3]), "s"(m[N - 2]), "s"(at[N - 2]), "s"(m[N - 1]), "s"(at[N - 1])
+                 : "memory");
+#undef TRN_COPY
 }
 
 // Every copy, load and store of this wave has landed.
