@@ -809,7 +809,7 @@ int trn_check(int dtype, int64_t m, int64_t c, int64_t f) {
 }
 
 struct TrnLayout {
-  size_t img, part, total;
+  size_t img, part, gsum, total;
   int nparts;
 };
 
@@ -821,16 +821,9 @@ TrnLayout trn_plan(bool bwd, int64_t m, int64_t f) {
   if (bwd) {
     L.nparts = triattn::trn_bwd_parts(m, (int)f);
     L.part = off;
-    const size_t parts =
-        round256((size_t)L.nparts * (size_t)triattn::trn_part_floats((int)f) * sizeof(float));
-    off += parts;
-    // The size reported is that of 40 KB images and a block of totals of their
-    // own.  The images are larger now and the totals lie in the first part's
-    // place, which needs less (4 KB per chunk against 33 KB), so a caller's
-    // workspace of the reported size keeps serving.
-    const size_t reported = round256(nch * 40960) + parts +
-                            round256(((size_t)triattn::TRN_C * 2 * f + 2 * f) * sizeof(float));
-    off = off > reported ? off : reported;
+    off += round256((size_t)L.nparts * (size_t)triattn::trn_part_floats((int)f) * sizeof(float));
+    L.gsum = off;
+    off += round256(((size_t)triattn::TRN_C * 2 * f + 2 * f) * sizeof(float));
   }
   L.total = off;
   return L;
@@ -920,7 +913,7 @@ int tri_transition_bwd(int dtype, int64_t m, int64_t c, int64_t f, const void* x
   char* b = (char*)workspace;
   a.img = b + L.img;
   a.part = (float*)(b + L.part);
-  a.gsum = a.part;  // the totals take the first part's place
+  a.gsum = (float*)(b + L.gsum);
   a.nparts = L.nparts;
   return triattn::launch_trn_bwd(a, (hipStream_t)stream) == hipSuccess ? TRIATTN_OK
                                                                         : TRIATTN_ERR_HIP;

@@ -31,3 +31,11 @@ def test_batched_and_row_ranges():
     for n, rows, size in ((32, 7, 187904), (100, 30, 3494656), (128, 16, 2687488),
                           (128, 1, 856576)):
         assert B.tri_attn_rows_bwd_workspace_bytes(B.BF16, n, rows, 4, 32) <= size
+
+
+@pytest.mark.parametrize("m,f,fwd,bwd", [(1, 128, 98304, 493568), (576, 256, 196608, 7706624),
+                                         (119025, 512, 393216, 51777536),
+                                         (65536, 2048, 1572864, 55328768)])
+def test_transition(m, f, fwd, bwd):
+    assert B.tri_transition_fwd_workspace_bytes(B.BF16, m, 128, f) <= fwd
+    assert B.tri_transition_bwd_workspace_bytes(B.BF16, m, 128, f) <= bwd
