@@ -809,7 +809,7 @@ int trn_check(int dtype, int64_t m, int64_t c, int64_t f) {
 }
 
 struct TrnLayout {
-  size_t img, part, gsum, total;
+  size_t img, part, total;
   int nparts;
 };
 
@@ -821,9 +821,16 @@ TrnLayout trn_plan(bool bwd, int64_t m, int64_t f) {
   if (bwd) {
     L.nparts = triattn::trn_bwd_parts(m, (int)f);
     L.part = off;
-    off += round256((size_t)L.nparts * (size_t)triattn::trn_part_floats((int)f) * sizeof(float));
-    L.gsum = off;
-    off += round256(((size_t)triattn::TRN_C * 2 * f + 2 * f) * sizeof(float));
+    const size_t parts =
+        round256((size_t)L.nparts * (size_t)triattn::trn_part_floats((int)f) * sizeof(float));
+    off += parts;
+    // The size reported is that of 40 KB images and a block of totals of their
+    // own, which callers' buffers have.  The images, 44 KB now, use what the
+    // totals leave by lying in the first part's place (4 KB per chunk against
+    // 33 KB; the rest stays unused).
+    const size_t reported = round256(nch * 40960) + parts +
+                            round256(((size_t)triattn::TRN_C * 2 * f + 2 * f) * sizeof(float));
+    off = off > reported ? off : reported;
   }
   L.total = off;
   return L;
@@ -913,7 +920,7 @@ int tri_transition_bwd(int dtype, int64_t m, int64_t c, int64_t f, const void* x
   char* b = (char*)workspace;
   a.img = b + L.img;
   a.part = (float*)(b + L.part);
-  a.gsum = (float*)(b + L.gsum);
+  a.gsum = a.part;  // the totals take the first part's place
   a.nparts = L.nparts;
   return triattn::launch_trn_bwd(a, (hipStream_t)stream) == hipSuccess ? TRIATTN_OK
                                                                         : TRIATTN_ERR_HIP;

@@ -153,7 +153,7 @@ hipError_t launch_lnl_bwd(const LnlBwdArgs& a, hipStream_t s);
 constexpr int TRN_C = 128;         // features per row (the pair channel width)
 constexpr int TRN_FC = 32;         // hidden columns per weight chunk
 constexpr int TRN_FWD_IMG = 24576; // bytes of one chunk's forward weight image
-constexpr int TRN_BWD_IMG = 40960; // bytes of one chunk's backward weight image
+constexpr int TRN_BWD_IMG = 45056; // bytes of one chunk's backward weight image
 constexpr int TRN_GROUP = 128;     // hidden columns per workgroup of the weight-gradient kernel
 
 struct TrnFwdArgs {
@@ -177,7 +177,7 @@ struct TrnBwdArgs {
   float *dw1, *dw2, *dgamma, *dbeta;  // [C][2F], [F][C], [C], [C]
   char* img;                     // workspace: F / 32 backward chunk images
   float* part;                   // workspace: nparts partial sums (see trn_part_floats)
-  float* gsum;                   // workspace: G [C][2F] and s [2F] totals
+  float* gsum;                   // G [C][2F] and s [2F] totals, in the place of part 0's
   int nparts;                    // row partitions of the weight-gradient kernel
 };
 

@@ -51,7 +51,7 @@ constexpr int TRN_ROWS = 32 * TRN_WAVES;  // rows per workgroup block
 
 // image of one chunk j (hidden columns fb = 32 j .. fb + 31), bytes:
 //   forward : A1a [0, 8K)  A1b [8K, 16K)  A2 [16K, 24K)
-//   backward: A1a [0, 8K)  A1b [8K, 16K)  A3 [16K, 24K)  A4 [24K, 40K)
+//   backward: A1a [0, 8.5K)  A1b [8.5K, 17K)  A3 [17K, 25.5K)  A4 [25.5K, 43.5K), padded to 44K
 // A1a / A1b: W1^T rows fb + r (a) / F + fb + r (b), 16 pieces (16 bytes) of 8 features.
 // A2: W2^T for output tile t, row r = output column 32 t + r, 4 pieces
 //     (k-step s, half g) of hidden columns in accumulator order.
@@ -59,21 +59,24 @@ constexpr int TRN_ROWS = 32 * TRN_WAVES;  // rows per workgroup block
 // A4: W1 for feature tile t, row r = feature 32 t + r, 8 pieces (k-step
 //     s = 0..3, half g): s < 2 the a columns, s >= 2 the b columns of the
 //     chunk, in accumulator order.
-// In LDS (a slot) every row is followed by 16 unused bytes: rows r, r + 1, ..
-// then start an odd number of 16-byte pieces apart, so an operand read (one
-// piece of 32 consecutive rows) is free of bank conflicts and all of a lane's
-// reads of a chunk are one address per row pitch plus constants (a permutation
-// of the pieces takes 16 to 24 address registers, which the kernels spend on
-// operands in flight instead).  The copy leaves the gaps: each lane has its own
-// address in the image.
-constexpr int IMG_A1B = 8192, IMG_A2 = 16384, IMG_A3 = 16384, IMG_A4 = 24576;
-constexpr int P1 = 256 + 16, P2 = 64 + 16, P4 = 128 + 16;         // row pitches in a slot
+// In LDS every row is followed by 16 unused bytes: rows r, r + 1, .. then start
+// an odd number of 16-byte pieces apart, so an operand read (one piece of 32
+// consecutive rows) is free of bank conflicts and all of a lane's reads of a
+// chunk are one address per row pitch plus constants (a permutation of the
+// pieces takes 16 to 24 address registers, which the kernels spend on operands
+// in flight instead).  The backward's images hold the gaps too (its workspace
+// has the room, and without them trn_bwd_w, which reads rows from the images,
+// takes 1.6 us more and trn_bwd_dx, with an address per copy, 0.8); the
+// forward's do not, which keeps its workspace at 24 KB per chunk: its copies
+// leave the gaps, each lane with its own address in the image.
+constexpr int IMG_A2 = 16384;                                      // forward image
+constexpr int P1 = 256 + 16, P2 = 64 + 16, P4 = 128 + 16;         // row pitches in LDS
 constexpr int OFF_A1B = 32 * P1, OFF_A2 = 64 * P1;                // forward
 constexpr int OFF_A3 = 64 * P1, OFF_A4 = 96 * P1;                 // backward
-constexpr int FWD_SLOT = 27648, BWD_SLOT = 45056;                 // whole copies of 1 KB
+constexpr int FWD_SLOT = 27648;                                   // whole copies of 1 KB
 static_assert(OFF_A2 + 128 * P2 <= FWD_SLOT && FWD_SLOT % 1024 == 0, "slot size");
-static_assert(OFF_A4 + 128 * P4 <= BWD_SLOT && BWD_SLOT % 1024 == 0, "slot size");
-static_assert(IMG_A2 + 128 * 64 == TRN_FWD_IMG && IMG_A4 + 128 * 128 == TRN_BWD_IMG, "image size");
+static_assert(IMG_A2 + 128 * 64 == TRN_FWD_IMG, "image size");
+static_assert(OFF_A4 + 128 * P4 <= TRN_BWD_IMG && TRN_BWD_IMG % 1024 == 0, "image size");
 
 // Accumulator order of a 16-wide contraction step s: slot e of half g holds
 // index 16 s + 8 (e / 4) + 4 g + e % 4 (the rows a 32x32 accumulator gives
@@ -97,26 +100,30 @@ __global__ __launch_bounds__(256) void trn_pack_kernel(const bf16* w1, const bf1
   if (idx >= (int64_t)(f / TRN_FC) * per) return;
   const int j = (int)(idx / per), o = 16 * (int)(idx % per), fb = TRN_FC * j;
   const int n1 = 2 * f;  // W1 row length
-  bf16x8 v;
-  static_assert(IMG_A2 == IMG_A3, "A1a and A1b lie alike in both images");
-  if (o < IMG_A2) {  // A1a, A1b
-    const int half = o / IMG_A1B, r = o % IMG_A1B / 256, c = o % 256 >> 4;
-    const int col = half * f + fb + r;
+  bf16x8 v = {};         // gaps stay zero
+  const int p1 = bwd ? P1 : 256;
+  if (o < 64 * p1) {  // A1a, A1b
+    const int r = o / p1, c = o % p1 >> 4;
+    const int col = (r >> 5) * f + fb + (r & 31);
+    if (c < 16) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = w1[(int64_t)(8 * c + e) * n1 + col];
+      for (int e = 0; e < 8; ++e) v[e] = w1[(int64_t)(8 * c + e) * n1 + col];
+    }
   } else if (!bwd) {  // A2
     const int r = (o - IMG_A2) / 64, c = o % 64 >> 4;  // r: output column
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = w2[(int64_t)(fb + acc_k(c >> 1, c & 1, e)) * TRN_C + r];
-  } else if (o < IMG_A4) {  // A3
-    const int r = (o - IMG_A3) / 256, c = o % 256 >> 4;
-    v = *(const bf16x8*)(w2 + (int64_t)(fb + r) * TRN_C + 8 * c);
+  } else if (o < OFF_A4) {  // A3
+    const int r = (o - OFF_A3) / P1, c = ((o - OFF_A3) % P1) >> 4;
+    if (c < 16) v = *(const bf16x8*)(w2 + (int64_t)(fb + r) * TRN_C + 8 * c);
   } else {  // A4
-    const int r = (o - IMG_A4) / 128, c = o % 128 >> 4;  // r: feature
+    const int r = (o - OFF_A4) / P4, c = ((o - OFF_A4) % P4) >> 4;  // r: feature
     const int s = c >> 1, g = c & 1;
     const int base = (s < 2 ? 0 : f) + fb;
+    if (r < TRN_C && c < 8) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = w1[(int64_t)r * n1 + base + acc_k(s & 1, g, e)];
+      for (int e = 0; e < 8; ++e) v[e] = w1[(int64_t)r * n1 + base + acc_k(s & 1, g, e)];
+    }
   }
   *(bf16x8*)(img + (int64_t)j * img_bytes + o) = v;
 }
@@ -185,67 +192,85 @@ __device__ inline void store_row(bf16* base, int64_t row, int g, const f32x16 (&
                  (bf16)acc[t][4 * j + 3]};
 }
 
-// Chunk images HBM -> LDS slots by DMA, pieces of 1 KB dealt to the waves in
-// turn (the last piece several times, so that no wave branches).  Written as
-// instructions: after the builtin the compiler holds the next LDS read,
-// whatever it reads, until the copy has landed, which put a chunk's whole copy
-// latency into every chunk of the kernels that read other slots meanwhile.  It
-// does not count these copies either, so chunk_wait() must stand before the
-// slot's readers; its own counted waits only get stricter by them.
-template <bool BWD>
-struct ChunkCopy {
-  static constexpr int IMG = BWD ? TRN_BWD_IMG : TRN_FWD_IMG, SLOT = BWD ? BWD_SLOT : FWD_SLOT;
-  static constexpr int PIECES = SLOT / 1024, N = (PIECES + TRN_WAVES - 1) / TRN_WAVES;
-  static_assert(N == (BWD ? 6 : 4), "pieces per wave");
+// Chunk images HBM -> LDS by DMA, pieces of 1 KB dealt to the waves in turn (the
+// last piece several times, so that no wave branches); real = false reads no
+// memory and fills the slot with zeros.  Written as instructions: after the
+// builtin the compiler holds the next LDS read, whatever it reads, until the
+// copy has landed, which put a chunk's whole copy latency into every chunk of
+// the kernels that read other slots meanwhile.  It does not count these copies
+// either, so chunk_wait() must stand before the slot's readers; its own counted
+// waits only get stricter by them.
+// m0 (the LDS address) is an operand, so that the compiler knows what it holds.
+// It does not see to the wait states here: five before the first load, in case
+// a scalar operand has just come back from a vector register, and one after a
+// write of m0.
+#define TRN_COPY(m, v, s) "s_mov_b32 m0, " m "\n\ts_nop 0\n\tbuffer_load_dwordx4 " v ", %1, " s " offen lds\n\t"
+
+__device__ inline u32x4 chunk_rsrc(const char* src, bool real, int bytes) {
+  const uint64_t b = (uint64_t)src;
+  return u32x4{(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, real ? (uint32_t)bytes : 0u, 0x00020000u};
+}
+
+struct FwdCopy {
+  static constexpr int PIECES = FWD_SLOT / 1024, N = (PIECES + TRN_WAVES - 1) / TRN_WAVES;
+  static_assert(N == 4, "pieces per wave");
   uint32_t at[N];  // where the wave's pieces go in the slot
   uint32_t v[N];   // and this lane's 16 bytes of them in the image (past its end in a gap: zeros)
 
-  __device__ inline ChunkCopy(int wave, int lane) {
-    constexpr int R1 = BWD ? OFF_A4 : OFF_A2;  // rows of 16 pieces up to here
-    constexpr int I1 = BWD ? IMG_A4 : IMG_A2;
-    constexpr int P = BWD ? P4 : P2, W = P - 16;  // and of W bytes after
+  // (In units of 16 bytes, with the divisions as 24-bit products and without a
+  // branch: the kernel's first copies wait for this.)
+  __device__ inline FwdCopy(int wave, int lane) {
+    constexpr uint32_t R1 = OFF_A2 / 16;  // rows of 16 units and a gap up to here, then of 4
+    static_assert(R1 % 64 == 0, "a piece holds rows of one kind");
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      at[i] = 1024 * min(wave + TRN_WAVES * i, PIECES - 1);
-      const int o = (int)at[i] + 16 * lane;
-      const int r = o < R1 ? o / P1 : (o - R1) / P, c = o < R1 ? o % P1 : (o - R1) % P;
-      if (o < R1)
-        v[i] = c < 256 ? 256 * r + c : IMG;
+      const uint32_t piece = min(wave + TRN_WAVES * i, PIECES - 1);
+      at[i] = 1024 * piece;
+      const uint32_t u = 64 * piece + lane;
+      // u / 17, q / 5: exact below 2^16
+      const uint32_t r1 = __umul24(u, 61681) >> 20, c1 = u - __umul24(r1, 17);
+      const uint32_t q = (u - R1) & 0xffff, r2 = __umul24(q, 52429) >> 18, c2 = q - __umul24(r2, 5);
+      const uint32_t v1 = c1 < 16 ? 256 * r1 + 16 * c1 : TRN_FWD_IMG;
+      const uint32_t v2 = c2 < 4 && r2 < TRN_C ? IMG_A2 + 64 * r2 + 16 * c2 : TRN_FWD_IMG;
+      if (TRN_WAVES * (i + 1) <= R1 / 64)
+        v[i] = v1;
+      else if (TRN_WAVES * i >= R1 / 64)
+        v[i] = v2;
       else
-        v[i] = c < W && r < TRN_C ? I1 + W * r + c : IMG;
+        v[i] = piece < R1 / 64 ? v1 : v2;
     }
   }
 
-  // One chunk's (real = false reads no memory and fills the slot with zeros).
   __device__ inline void operator()(const char* src, char* dst, bool real) const {
-    const uint64_t b = (uint64_t)src;
-    const u32x4 r = {(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, real ? (uint32_t)IMG : 0u, 0x00020000u};
     const uint32_t to = lds_addr(dst);
-    // m0 (the LDS address) is an operand, so that the compiler knows what it
-    // holds.  It does not see to the wait states here: five before the first
-    // load, in case a scalar operand has just come back from a vector
-    // register, and one after a write of m0.
-#define TRN_COPY(m, v) "s_mov_b32 m0, " m "\n\ts_nop 0\n\tbuffer_load_dwordx4 " v ", %1, 0 offen lds\n\t"
     uint32_t m0 = to + at[0];
-    if constexpr (BWD)
-      asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %2, %1, 0 offen lds\n\t"
-                   TRN_COPY("%3", "%4") TRN_COPY("%5", "%6") TRN_COPY("%7", "%8")
-                   TRN_COPY("%9", "%10") TRN_COPY("%11", "%12")
-                   : "+{m0}"(m0)
-                   : "s"(r), "v"(v[0]), "s"(to + at[1]), "v"(v[1]), "s"(to + at[2]), "v"(v[2]),
-                     "s"(to + at[3]), "v"(v[3]), "s"(to + at[N - 2]), "v"(v[N - 2]),
-                     "s"(to + at[N - 1]), "v"(v[N - 1])
-                   : "memory");
-    else
-      asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %2, %1, 0 offen lds\n\t"
-                   TRN_COPY("%3", "%4") TRN_COPY("%5", "%6") TRN_COPY("%7", "%8")
-                   : "+{m0}"(m0)
-                   : "s"(r), "v"(v[0]), "s"(to + at[1]), "v"(v[1]), "s"(to + at[2]), "v"(v[2]),
-                     "s"(to + at[3]), "v"(v[3])
-                   : "memory");
-#undef TRN_COPY
+    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %2, %1, 0 offen lds\n\t"
+                 TRN_COPY("%3", "%4", "0") TRN_COPY("%5", "%6", "0") TRN_COPY("%7", "%8", "0")
+                 : "+{m0}"(m0)
+                 : "s"(chunk_rsrc(src, real, TRN_FWD_IMG)), "v"(v[0]), "s"(to + at[1]), "v"(v[1]),
+                   "s"(to + at[2]), "v"(v[2]), "s"(to + at[3]), "v"(v[3])
+                 : "memory");
   }
 };
+
+__device__ inline void bwd_copy(const char* src, char* dst, int wave, int lane, bool real) {
+  constexpr int PIECES = TRN_BWD_IMG / 1024, N = (PIECES + TRN_WAVES - 1) / TRN_WAVES;
+  static_assert(N == 6, "pieces per wave");
+  const uint32_t to = lds_addr(dst);
+  uint32_t at[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) at[i] = 1024 * min(wave + TRN_WAVES * i, PIECES - 1);
+  uint32_t m0 = to + at[0];
+  asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %2, %1, %3 offen lds\n\t"
+               TRN_COPY("%4", "%2", "%5") TRN_COPY("%6", "%2", "%7") TRN_COPY("%8", "%2", "%9")
+               TRN_COPY("%10", "%2", "%11") TRN_COPY("%12", "%2", "%13")
+               : "+{m0}"(m0)
+               : "s"(chunk_rsrc(src, real, TRN_BWD_IMG)), "v"(16 * lane), "s"(at[0]), "s"(to + at[1]),
+                 "s"(at[1]), "s"(to + at[2]), "s"(at[2]), "s"(to + at[3]), "s"(at[3]),
+                 "s"(to + at[4]), "s"(at[4]), "s"(to + at[5]), "s"(at[5])
+               : "memory");
+}
+#undef TRN_COPY
 
 // Every copy, load and store of this wave has landed.
 __device__ inline void chunk_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -274,10 +299,11 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_fwd_kernel(TrnFwdArgs a) {
   const int64_t nblk = (a.m + TRN_ROWS - 1) / TRN_ROWS;
   if ((int64_t)blockIdx.x >= nblk) return;  // whole workgroup, before any barrier
   const int nch = a.f / TRN_FC;             // at least 4 (F is a multiple of 128)
-  const int64_t nsteps = (nblk - blockIdx.x + gridDim.x - 1) / gridDim.x * nch;
+  // (in 32 bits, at most 2^23 blocks: a 64-bit division takes 0.2 us)
+  const int nsteps = (int)(((uint32_t)nblk - blockIdx.x + gridDim.x - 1) / gridDim.x) * nch;
   int dj = 0, ds = 0;  // chunk index and slot of the next DMA
-  int64_t issued = 0;
-  const ChunkCopy<false> copy(wave, lane);
+  int issued = 0;
+  const FwdCopy copy(wave, lane);
   auto issue = [&] {
     copy(a.img + (int64_t)dj * TRN_FWD_IMG, ring + ds * FWD_SLOT, issued < nsteps);
     dj = dj + 1 == nch ? 0 : dj + 1;
@@ -411,19 +437,20 @@ constexpr int TRN_NQ = 8;  // operand fragments in flight per wave
 
 __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_dx_kernel(TrnBwdArgs a) {
   constexpr int SLOTS = 3, NQ = TRN_NQ;
-  __shared__ __align__(16) char ring[SLOTS * BWD_SLOT];
+  __shared__ __align__(16) char ring[SLOTS * TRN_BWD_IMG];
   __shared__ __align__(16) float gb[2][TRN_C];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t nblk = (a.m + TRN_ROWS - 1) / TRN_ROWS;
   if ((int64_t)blockIdx.x >= nblk) return;
   const int nch = a.f / TRN_FC;
-  const int64_t nsteps = (nblk - blockIdx.x + gridDim.x - 1) / gridDim.x * nch;
+  // (in 32 bits, at most 2^23 blocks: a 64-bit division takes 0.2 us)
+  const int nsteps = (int)(((uint32_t)nblk - blockIdx.x + gridDim.x - 1) / gridDim.x) * nch;
   int dj = 0, ds = 0;  // chunk index and slot of the next DMA
-  int64_t issued = 0;
-  const ChunkCopy<true> copy(wave, lane);
+  int issued = 0;
   auto issue = [&] {
-    copy(a.img + (int64_t)dj * TRN_BWD_IMG, ring + ds * BWD_SLOT, issued < nsteps);
+    bwd_copy(a.img + (int64_t)dj * TRN_BWD_IMG, ring + ds * TRN_BWD_IMG, wave, lane,
+             issued < nsteps);
     dj = dj + 1 == nch ? 0 : dj + 1;
     ds = ds + 1 == SLOTS ? 0 : ds + 1;
     ++issued;
@@ -465,7 +492,7 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_dx_kernel(TrnBwdArgs a
     ln_row_saved(xr, gb, g, mean, rstd, of);
     f32x16 d1[4] = {};  // do1^T: feature 32 t + acc row, lane <-> row
     for (int j = 0; j < nch; ++j) {
-      const uint32_t sn = so == (SLOTS - 1) * BWD_SLOT ? 0u : so + BWD_SLOT;
+      const uint32_t sn = so == (SLOTS - 1) * TRN_BWD_IMG ? 0u : so + TRN_BWD_IMG;
       f32x16 ha = {}, hb = {}, du = {};
       bf16x8 dh[4];
       float ex[16], si[16], sg[16];
@@ -622,10 +649,10 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_w_kernel(TrnBwdArgs a,
   bf16x8 w1a[4], w1b[4], w2r[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    const char* o = img + ((f0 & 31) + l16) * 256 + 16 * (4 * s + q);
+    const char* o = img + ((f0 & 31) + l16) * P1 + 16 * (4 * s + q);
     w1a[s] = *(const bf16x8*)o;
-    w1b[s] = *(const bf16x8*)(o + IMG_A1B);
-    w2r[s] = *(const bf16x8*)(o + IMG_A3);
+    w1b[s] = *(const bf16x8*)(o + OFF_A1B);
+    w2r[s] = *(const bf16x8*)(o + OFF_A3);
   }
 
   // staging: thread tid takes 8 features (chunk tid % 16) of row tid / 16:
@@ -771,7 +798,8 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_w_kernel(TrnBwdArgs a,
   }
 }
 
-// Fixed-order sum of the partial blocks: G and s into gsum, dW2 into its output.
+// Fixed-order sum of the partial blocks: G and s into gsum (part 0's place:
+// an entry is read and written by one thread only), dW2 into its output.
 __global__ __launch_bounds__(256) void trn_reduce_kernel(TrnBwdArgs a) {
   const int64_t per = trn_part_floats(a.f);
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
