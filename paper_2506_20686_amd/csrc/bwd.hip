@@ -146,8 +146,10 @@ __device__ inline void bwd_pad(const Geom& G, int block, float* lse2, float* dsu
 // pair row).  Measured in one launch at N = 384 / 768 (32 channels) and 333
 // (64 channels): 39.5 / 160 / 58.5 us, what the elementwise step took by
 // itself; the other pieces (11, 14 and 17 us as launches of their own) run
-// under it.  Four waves per SIMD feed the HBM as well as eight, and 64
-// registers (eight waves) spill the bias piece: 167 us at N = 768.
+// under it.  A shorter step covers them less: for 96 rows of N = 768 it takes
+// 27 us instead of 21, where the pieces took about 14.  Four waves per SIMD
+// feed the HBM as well as eight, and 64 registers (eight waves) spill the bias
+// piece: 167 us at N = 768.
 struct BwdPrepGrid {
   int nkb, nprep, npad, ew;
 };
@@ -1330,8 +1332,8 @@ hipError_t launch_bwd(const Geom& g, int node, const Prep& p, const BwdWs& ws, c
     pg.nprep = (int)prep_blocks(g, node);
     pg.npad = (int)(((int64_t)g.H * g.nr * (g.np - g.n) + 255) / 256);
     pg.ew = (tph * g.n * g.H + 255) / 256;
-    // (a pair map whose grid passes 2^32 threads, n nr H >= 2^30, has tensors
-    // of 34 GB and up, a dozen of which no card holds)
+    // (a pair map whose grid passes 2^32 threads, n nr H >= 2^30, or 2^31 at 16
+    // channels, has tensors of 69 GB and up, a dozen of which no card holds)
     const dim3 grid((unsigned)(pg.nprep + pg.npad) + (unsigned)pg.ew * (unsigned)g.nr, 1,
                     (unsigned)g.batch);
     auto go = [&](auto kernel) {

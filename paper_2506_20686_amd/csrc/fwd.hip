@@ -105,9 +105,10 @@ struct SoftmaxState {
 // channels per head.  The fp32 matrix rate bounds it (a 32x32 tile of 32
 // channels is 32 MFMAs of 64 cycles), so the row sums of P are vector adds:
 // on the matrix cores they were 16 more MFMAs per tile.  With one pair of
-// bias tiles in registers (162 -> 128) it runs four waves per SIMD.
-// 193 x 193 pairs, 4 heads of 32 channels: 88 -> 64 us (69 with the row sums
-// alone); 384: 377 -> 288 us; 300, 64 channels: 415 -> 352 us.
+// bias tiles in registers (162 -> 128) it runs four waves per SIMD at 32 channels
+// (two at 64, whose blocks take 72 KB of LDS).  The whole forward call, 193 x 193
+// pairs, 4 heads of 32 channels: 90.5 -> 62 us; the kernel, 384: 377 -> 288 us;
+// 300, 64 channels: 415 -> 352 us.
 template <typename T, int D>
 __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs<T> a) {
   to_sample(a);

@@ -895,8 +895,11 @@ __global__ __launch_bounds__(64 * LBG_WAVES) void lnl_bwd_g_kernel(LnlBwdArgs a)
 // would take 208 of the 256 registers and the compiler then keeps tiles in
 // scratch, which waits for the copies in flight; three fit (240), so the
 // fourth output's sums take a pass over x and that output alone: 353 us for
-// both against 468.  128,128,128 columns: one
-// pass, 225 against 381 us.
+// both against 468 on a card that has been idle; over the launches of a run,
+// as the clock follows the load, 235 to 310 (dx) and 110 to 123 us.  That
+// second pass moves 2.9 TB/s, less than half of a read stream's rate: its waves
+// wait for memory 60% of their life, two units in flight.  128,128,128 columns:
+// one pass, 225 against 381 us.
 //
 // Slot rows are 256 bytes (one 128-column row of x or of an output), chunk c
 // (8 columns) of row p at chunk slot c ^ (4 (p % 4) + (p / 4) % 4): 16

@@ -20,7 +20,7 @@ namespace triattn {
 // starting node reads bias[q][k][h], the ending node bias[k][q][h].
 //
 // One workgroup per 32 x 32 block (query tile qa, key tile kb) of the map,
-// one head at a time: the block goes through LDS once and leaves as bt tile
+// four heads at a time: the block goes through LDS once and leaves as bt tile
 // (qa, kb) and btT tile (kb, qa), both written 16 bytes per thread.
 template <typename T>
 __device__ inline void load_heads4(const T* p, float (&x)[4]);

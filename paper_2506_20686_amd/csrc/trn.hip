@@ -286,10 +286,13 @@ __device__ inline void chunk_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "mem
 // operand fragments are in flight per wave, across chunks.  The next block's
 // rows are loaded ahead of this block's stores (loads and stores retire in
 // order).  Weights copied through registers and reads left to the compiler
-// measured 61.8 us at m = 345^2, F = 512 (forward call), against 59.4.  A
-// fragment per MFMA is the LDS's whole bandwidth at the MFMA's full rate.
-// 64 rows per wave halve that, but at one wave per SIMD the same schedule
-// (442 registers) took 71.6 us.
+// measured 61.8 us at m = 345^2, F = 512 (forward call), against 59.4.  No unit
+// is full (m = 768^2): the matrix cores are busy 44% of the time, the LDS 24%
+// (a fragment per MFMA is half of its 256 bytes per clock at the MFMA's full
+// rate), and the waves wait for memory or the barrier 26% of theirs and are
+// ready without being issued 43%: two waves per SIMD do not cover each other's
+// latencies.  64 rows per wave halve the reads, but at one wave per SIMD the
+// same schedule (442 registers) took 71.6 us.
 __global__ __launch_bounds__(TRN_THREADS, 1) void trn_fwd_kernel(TrnFwdArgs a) {
   constexpr int SLOTS = 3;
   __shared__ __align__(16) char ring[SLOTS * FWD_SLOT];
@@ -429,9 +432,10 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_fwd_kernel(TrnFwdArgs a) {
 // registers and reads left to the compiler (one fragment ahead) measured
 // 483 us at m = 768^2, F = 512, against 456 us on the same card (845 TFLOP/s
 // of the ten products).  Of what remains the operand reads, one LDS fragment
-// per MFMA, cost most (without them, a third less); 64 rows per wave would
-// halve them, but at one wave per SIMD the forward built that way was slower
-// (314 against 268 us).
+// per MFMA, cost most (without them, a third less), by their latency and issue:
+// the LDS is busy 23% of the time, the matrix cores 42%.  64 rows per wave
+// would halve them, but at one wave per SIMD the forward built that way was
+// slower (314 against 268 us).
 
 constexpr int TRN_NQ = 8;  // operand fragments in flight per wave
 
@@ -598,11 +602,13 @@ __global__ __launch_bounds__(TRN_THREADS, 1) void trn_bwd_dx_kernel(TrnBwdArgs a
 // and did the elementwise step in both lanes of a pair: 88 instead of 80
 // (half-size) MFMA slots, 350 instead of 243 vector instructions and 44
 // instead of 40 KB of LDS reads per wave and block: 0.87 ms at m = 768^2,
-// F = 512, against 0.65-0.68 ms now (1140 TFLOP/s of the MFMAs it issues).  A
-// loop of nothing but this mix of MFMAs, LDS reads and vector instructions
+// F = 512, against 0.68-0.78 ms now (770 GFLOP of MFMAs: 990-1140 TFLOP/s; the
+// launches of one run differ from 0.70 to 0.95 as the clock follows the load).
+// A loop of nothing but this mix of MFMAs, LDS reads and vector instructions
 // (80 : 56 : 280), two waves per SIMD on random operands, takes 2.24 us per
-// block, 0.645 ms for this shape: what bounds the kernel now is issue and
-// the clock under that load, not latency.  Four waves of 32 columns (one per
+// block, 0.645 ms for this shape: issue and the clock under that load bound the
+// kernel.  Its matrix cores are busy 49% of the time, its LDS 45%, a third of
+// that for bank conflicts.  Four waves of 32 columns (one per
 // SIMD, 490 registers) measured 0.735 ms: one wave issues at most an
 // instruction every four to five cycles.
 // The x and dout tiles are stored as four 32-column blocks of 64-byte rows
